@@ -1,0 +1,95 @@
+"""Traces whose scenarios do not all fit the device at once run in several launches, and
+pools of up to 1024 sequences per instance keep their queues on chip: choices, TTFTs,
+realised TTFTs and final states against the oracle, bit for bit."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from gpu_util import assert_state_equal, bits, gpu_trace, gpu_trace_realized  # noqa: E402
+from oracle import oracle as O  # noqa: E402
+from workloads import make_tiny_workload  # noqa: E402
+
+
+@pytest.mark.parametrize("n_inst,n_scen,mcap,n_q,what", [
+    (17, 129, None, 20, "two workgroups of 16 waves each: 258 do not fit, two launches"),
+    (17, 300, None, 12, "three launches of 100 scenarios"),
+    (33, 171, None, 12, "three workgroups per scenario, three launches of 57"),
+    (6, 700, None, 12, "one workgroup per scenario: one launch of any size"),
+    (3, 700, None, 12, "one 4-wave workgroup per scenario"),
+    (9, 260, 300, 12, "8 slots per lane: two 8-wave workgroups, three launches"),
+    (5, 140, 1000, 12, "16 slots per lane: two 4-wave workgroups, two launches"),
+    (4, 300, 1000, 12, "16 slots per lane, one workgroup per scenario"),
+    (1100, 2, None, 8, "more instances than 64 workgroups hold: the HBM-state kernel"),
+])
+def test_trace_parts(n_inst, n_scen, mcap, n_q, what):
+    wl = make_tiny_workload(40 + n_inst, n_inst=n_inst, max_res=4, n_q=n_q, n_scen=n_scen)
+    choice, chosen, util, ctx = gpu_trace(wl, queue_cap=64, max_seqs_cap=mcap)
+    for z in sorted({0, n_scen // 2 - 1, n_scen // 2, n_scen - 1} | set(range(0, n_scen, 23))):
+        ref = O.trace(wl, scenario=z, queue_cap=64)
+        np.testing.assert_array_equal(choice[z], ref.choice, err_msg=f"scenario {z}")
+        np.testing.assert_array_equal(bits(chosen[z]), bits(ref.ttft_chosen))
+        np.testing.assert_array_equal(bits(util[z]), bits(ref.util_chosen))
+        assert_state_equal(ctx, z, ref)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n_inst,n_scen,mcap", [(17, 131, None), (6, 5, 1024)])
+def test_trace_parts_realized(n_inst, n_scen, mcap):
+    """The same with first tokens tracked, under the constrained objective."""
+    wl = make_tiny_workload(90 + n_inst, n_inst=n_inst, max_res=4, n_q=25, n_scen=n_scen)
+    tau = O.ttft_targets(wl.q_prefill, wl.tau_u_ms, wl.tau_v) * 0.05
+    choice, chosen, real, ctx = gpu_trace_realized(wl, tau=tau, queue_cap=64, max_seqs_cap=mcap)
+    for z in sorted({0, n_scen // 2, n_scen - 1}):
+        ref = O.trace(wl, scenario=z, queue_cap=64, tau=tau)
+        np.testing.assert_array_equal(choice[z], ref.choice, err_msg=f"scenario {z}")
+        np.testing.assert_array_equal(bits(chosen[z]), bits(ref.ttft_chosen))
+        np.testing.assert_array_equal(bits(real[z]), bits(ref.realized))
+        assert_state_equal(ctx, z, ref)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n_inst,n_scen,mcap", [(17, 131, None), (5, 2, 1024)])
+def test_trace_parts_captured(n_inst, n_scen, mcap):
+    """The launches of such a trace captured in a graph: every replay gives the eager
+    run's results, with eager work and a synchronisation between replays."""
+    from paper_2607_18253_amd import context_for
+    from gpu_util import T
+    wl = make_tiny_workload(7 + n_inst, n_inst=n_inst, max_res=4, n_q=20, n_scen=n_scen)
+    s = torch.cuda.Stream()
+    ctx = context_for(wl, stream=s, queue_cap=64, max_seqs_cap=mcap)
+    args = (T(wl.q_prefill, torch.int32), T(wl.q_decode, torch.int32),
+            T(wl.q_t_ms, torch.float64), float(wl.q_t_ms[-1]), T(wl.acc, torch.float64),
+            T(wl.cost, torch.float64), T(wl.w_cost, torch.float64), T(wl.w_lat_ms, torch.float64))
+    choice = torch.zeros((n_scen, wl.n_q), dtype=torch.int32, device="cuda:0")
+    chosen = torch.zeros((n_scen, wl.n_q), dtype=torch.float64, device="cuda:0")
+
+    def step():
+        ctx.reload_state()
+        ctx.advance(float(wl.q_t_ms[0]))
+        ctx.route_trace(*args, choice=choice, chosen_ttft=chosen)
+
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        step()
+    s.synchronize()
+    want = choice.clone(), chosen.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        step()
+    for _ in range(3):
+        choice.zero_()
+        chosen.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            g.replay()
+        s.synchronize()
+        assert torch.equal(choice, want[0])
+        assert torch.equal(chosen.view(torch.int64), want[1].view(torch.int64))
+    ctx.sync()
+    ctx.close()
