@@ -598,14 +598,10 @@ lar_status lar_route_step(lar_ctx* ctx, const int32_t* q_prefill, const int32_t*
     return fail(ctx, LAR_E_ARG, "null argument");
   if (n_cols <= ctx->max_col)
     return fail(ctx, LAR_E_ARG, "n_cols %d does not cover instance column %d", n_cols, ctx->max_col);
-  // the four calls of one routing step, every query value read from device memory
-  const LaunchEnv env = env_of(ctx);
-  HIP_TRY(ctx, lar::launch_traj(env, t_ms, 0.0));
-  HIP_TRY(ctx, lar::launch_est(env, 1, q_prefill, t_ms, 0.0, ctx->row_ttft, nullptr));
-  HIP_TRY(ctx, lar::launch_route(env, 1, ctx->row_ttft, (int64_t)ctx->I, acc, cost, n_cols,
-                                 w_cost, tau_ms ? w_cost : w_lat, tau_ms, choice, chosen_ttft,
-                                 utility, 1, 0));
-  HIP_TRY(ctx, lar::launch_commit(env, choice, 1, q_prefill, q_decode, 0, 0, t_next_ms, 0.0));
+  // estimate, route and commit of one query, every value read from device memory
+  const lar::StepArgs sa{q_prefill, q_decode, t_ms, t_next_ms, ctx->row_ttft, acc, cost, w_cost,
+                         tau_ms ? w_cost : w_lat, tau_ms, choice, chosen_ttft, utility};
+  HIP_TRY(ctx, lar::launch_step(env_of(ctx), sa));
   return LAR_OK;
 }
 

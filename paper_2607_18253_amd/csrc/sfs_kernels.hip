@@ -31,13 +31,136 @@
 
 namespace lar {
 
+// ------------------------------------------------------------------ estimates
+// The background of one instance as k_traj leaves it, in registers, and each query's
+// own continuation from it.
+struct EstBack {
+  Coef k;
+  int ok;
+  double E0;
+  int64_t it0;
+  int lft, P0, D0;        // P <= B and D <= M fit in 32 bits
+  int64_t C0, A0;
+  int K, D1;              // the first decode-tail batch, which nearly every query reaches
+  int64_t C1;
+  bool need_C, need_A;
+  double dz, ez;
+
+  __device__ __forceinline__ void load(const DevParams& pr, const DevTraj& tr, int qid, int j) {
+    k = load_coef(pr, j);
+    ok = tr.ok[qid];
+    E0 = tr.E[qid];
+    it0 = (int64_t)tr.pre[qid] + 1;
+    lft = tr.left[qid];
+    P0 = (int)tr.P[qid];
+    D0 = (int)tr.D[qid];
+    C0 = tr.C[qid];
+    A0 = tr.A[qid];
+    K = tail_count(tr);
+    D1 = K > 0 ? tr.tailD[qid] : 0;
+    C1 = K > 0 ? tr.tailC[qid] : 0;
+    // Batch time of Sec. 4.1 with batch_time's operations: the context and attention
+    // terms are converted only where their coefficient is non-zero (lanes whose
+    // instances all have d = 0 or e = 0 skip them); otherwise the term is coef * 0.0.
+    need_C = k.d != 0.0;
+    need_A = k.e != 0.0;
+    dz = __dmul_rn(k.d, 0.0);
+    ez = __dmul_rn(k.e, 0.0);
+  }
+  __device__ __forceinline__ double bt_pd(int P, int D) const {
+    return __dadd_rn(__dadd_rn(k.a, __dmul_rn(k.b, (double)P)), __dmul_rn(k.c, (double)D));
+  }
+  __device__ __forceinline__ double bt_ca(double t, int64_t C, int64_t A) const {
+    double td = dz, te = ez;
+    if (need_C) td = __dmul_rn(k.d, (double)C);
+    if (need_A) te = __dmul_rn(k.e, (double)A);
+    return __dadd_rn(__dadd_rn(t, td), te);
+  }
+  // TTFT of a query of p prompt tokens that arrives at t; it_out: its batches (-1 when
+  // it has no estimate: NaN, with the error set).
+  __device__ __forceinline__ double query(const DevTraj& tr, int qid, int ZI, int p, double t,
+                                          int max_prompt, int reading, int64_t max_iters,
+                                          int32_t* err, int32_t* it_out) const {
+    *it_out = -1;
+    if (p < 1 || p > max_prompt) {
+      set_error(err, kErrArg);
+      return __builtin_nan("");
+    }
+    if (!ok) {
+      set_error(err, kErrIter);   // a clock behind t was already reported as a state error
+      return __builtin_nan("");
+    }
+    int64_t it = it0;
+    // admission batch: background features plus the query's first chunk (context 0)
+    const int ch = p < lft ? p : lft;
+    double E = __dadd_rn(
+        E0, bt_ca(bt_pd(P0 + ch, D0), C0, need_A ? A0 + (int64_t)ch * (ch + 1) / 2 : 0));
+    int rem = p - ch;
+    int cxq = ch;
+    bool done = reading == 1 && rem == 0;
+    int kk = 0;
+    while (!done) {
+      if (kk >= K) {   // cannot happen for p <= max_prompt; guard the tail bounds
+        set_error(err, kErrIter);
+        E = __builtin_nan("");
+        break;
+      }
+      const int Dk = kk == 0 ? D1 : tr.tailD[(int64_t)kk * ZI + qid];
+      const int64_t Ck = kk == 0 ? C1 : tr.tailC[(int64_t)kk * ZI + qid];
+      if (rem > 0) {
+        const int room = k.B - Dk;
+        const int c2 = rem < room ? rem : room;
+        E = __dadd_rn(E, bt_ca(bt_pd(c2, Dk), Ck,
+                               need_A ? (int64_t)c2 * cxq + (int64_t)c2 * (c2 + 1) / 2 : 0));
+        rem -= c2;
+        cxq += c2;
+        done = reading == 1 && rem == 0;
+      } else {
+        E = __dadd_rn(E, bt_ca(bt_pd(0, Dk + 1), Ck + cxq, 0));
+        done = true;
+      }
+      ++kk;
+      ++it;
+    }
+    if (it > max_iters) set_error(err, kErrIter);
+    *it_out = (int32_t)it;
+    return __dsub_rn(E, t);
+  }
+};
+
+// The one query of a routing step, and its estimate in the wave that has just stored
+// queue qid's trajectory.
+struct StepQuery {
+  const int32_t* p;
+  int max_prompt, reading;
+  double* ttft;   // [Z][I]
+};
+__device__ __forceinline__ void step_estimate(const DevParams& pr, const DevTraj& tr, int qid,
+                                              int j, int ZI, double t, int64_t max_iters,
+                                              int32_t* err, const StepQuery& sq) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  if (lane_id() == 0) {
+    EstBack b;
+    b.load(pr, tr, qid, j);
+    int32_t it;
+    sq.ttft[qid] =
+        b.query(tr, qid, ZI, *sq.p, t, sq.max_prompt, sq.reading, max_iters, err, &it);
+  }
+}
+
 // ------------------------------------------------------------------ k_traj
 // NC: some instance has d != 0, so the walk keeps context sums per batch; without
 // them an instance with d != 0 runs the engine.
-template <int KS, bool NC>
+// STEP: a routing step's first launch; the one query's estimate follows from the
+// trajectory in the same wave, which reads back what its own lane 0 stored (made visible
+// by the fence), so the walk is the what-if's.  With the route in the commit
+// (k_commit<KS, true>) a step is two launches instead of four:
+// 4 instances, a step from the host 17.0 -> 11.4 us, its kernels 12.3 -> 10.2 us.
+template <int KS, bool NC, bool STEP>
 __global__ __launch_bounds__(kWave) void k_traj(DevState S, DevParams pr, DevTraj tr, int Z, int I,
                                                const double* t_ptr, double t_val,
-                                               int64_t max_iters, int32_t* err) {
+                                               int64_t max_iters, int32_t* err, StepQuery sq) {
   const int qid = blockIdx.x;
   if (qid >= Z * I) return;
   const int j = qid % I;
@@ -61,7 +184,10 @@ __global__ __launch_bounds__(kWave) void k_traj(DevState S, DevParams pr, DevTra
                       : walk_traj<KS, NC, false, false>(S, e, qid, tr, Z * I, t, max_iters, err,
                                                         walk_lds);
   }
-  if (walked) return;
+  if (walked) {
+    if constexpr (STEP) step_estimate(pr, tr, qid, j, Z * I, t, max_iters, err, sq);
+    return;
+  }
   // the engine, for queues outside what the walk covers
   Queue<KS> w;
   w.load(S, e, qid);
@@ -128,29 +254,30 @@ __global__ __launch_bounds__(kWave) void k_traj(DevState S, DevParams pr, DevTra
       tr.tailC[(int64_t)kk * ZI + qid] = C;
     }
   }
+  if constexpr (STEP) step_estimate(pr, tr, qid, j, Z * I, t, max_iters, err, sq);
 }
 
 // ------------------------------------------------------------------ k_est
-// One block per (scenario, chunk of kEstChunk queries, 256 instances), one thread
-// per instance: the thread keeps its instance's trajectory in registers and walks
-// the chunk's queries (their prompt lengths staged in LDS), so each wave writes 64
-// consecutive estimates per query.
+// One block per (scenario, chunk of queries, 256 instances), one thread per instance:
+// the thread keeps its instance's trajectory in registers and walks the chunk's
+// queries (their prompt lengths staged in LDS), so each wave writes 64 consecutive
+// estimates per query.  chunk: at most kEstChunk, see launch_est.
 constexpr int kEstChunk = 16;
 
 __global__ __launch_bounds__(256) void k_est(DevParams pr, DevTraj tr, int Z, int Q, int I,
-                                            const int32_t* q_prefill, const double* t_ptr,
-                                            double t_val, int max_prompt,
+                                            int chunk, const int32_t* q_prefill,
+                                            const double* t_ptr, double t_val, int max_prompt,
                                             int reading, int64_t max_iters, double* ttft,
                                             int32_t* iters, int32_t* err) {
   __shared__ int s_p[kEstChunk];
-  const int n_chunks = (Q + kEstChunk - 1) / kEstChunk;
+  const int n_chunks = (Q + chunk - 1) / chunk;
   const int col_blocks = (I + 255) / 256;
   const int cb = (int)(blockIdx.x % (unsigned)col_blocks);
   const int zc = (int)(blockIdx.x / (unsigned)col_blocks);
   const int c = zc % n_chunks;
   const int z = zc / n_chunks;
-  const int q0 = c * kEstChunk;
-  const int q1 = Q - q0 < kEstChunk ? Q : q0 + kEstChunk;
+  const int q0 = c * chunk;
+  const int q1 = Q - q0 < chunk ? Q : q0 + chunk;
   if ((int)threadIdx.x < q1 - q0) s_p[threadIdx.x] = q_prefill[q0 + threadIdx.x];
   __syncthreads();
   const int j = cb * 256 + (int)threadIdx.x;
@@ -158,82 +285,13 @@ __global__ __launch_bounds__(256) void k_est(DevParams pr, DevTraj tr, int Z, in
   const int qid = z * I + j;
   const int ZI = Z * I;
   const double t = t_ptr ? *t_ptr : t_val;
-  const Coef k = load_coef(pr, j);
-  const int ok = tr.ok[qid];
-  const double E0 = tr.E[qid];
-  const int64_t it0 = (int64_t)tr.pre[qid] + 1;
-  const int lft = tr.left[qid];
-  // P <= B and D <= M fit in 32 bits
-  const int P0 = (int)tr.P[qid], D0 = (int)tr.D[qid];
-  const int64_t C0 = tr.C[qid], A0 = tr.A[qid];
-  const int K = tail_count(tr);
-  // the first decode-tail batch, which nearly every query reaches
-  const int D1 = K > 0 ? tr.tailD[qid] : 0;
-  const int64_t C1 = K > 0 ? tr.tailC[qid] : 0;
-  // Batch time of Sec. 4.1 with batch_time's operations: the context and attention
-  // terms are converted only where their coefficient is non-zero (lanes whose
-  // instances all have d = 0 or e = 0 skip them); otherwise the term is coef * 0.0.
-  const bool need_C = k.d != 0.0, need_A = k.e != 0.0;
-  const double dz = __dmul_rn(k.d, 0.0), ez = __dmul_rn(k.e, 0.0);
-  auto bt_pd = [&](int P, int D) {
-    return __dadd_rn(__dadd_rn(k.a, __dmul_rn(k.b, (double)P)), __dmul_rn(k.c, (double)D));
-  };
-  auto bt_ca = [&](double t, int64_t C, int64_t A) {
-    double td = dz, te = ez;
-    if (need_C) td = __dmul_rn(k.d, (double)C);
-    if (need_A) te = __dmul_rn(k.e, (double)A);
-    return __dadd_rn(__dadd_rn(t, td), te);
-  };
+  EstBack b;
+  b.load(pr, tr, qid, j);
   for (int q = q0; q < q1; ++q) {
     const int64_t o = ((int64_t)z * Q + q) * I + j;
-    const int p = s_p[q - q0];
-    if (p < 1 || p > max_prompt) {
-      set_error(err, kErrArg);
-      ttft[o] = __builtin_nan("");
-      if (iters) iters[o] = -1;
-      continue;
-    }
-    if (!ok) {
-      set_error(err, kErrIter);   // a clock behind t was already reported as a state error
-      ttft[o] = __builtin_nan("");
-      if (iters) iters[o] = -1;
-      continue;
-    }
-    int64_t it = it0;
-    // admission batch: background features plus the query's first chunk (context 0)
-    const int ch = p < lft ? p : lft;
-    double E = __dadd_rn(
-        E0, bt_ca(bt_pd(P0 + ch, D0), C0, need_A ? A0 + (int64_t)ch * (ch + 1) / 2 : 0));
-    int rem = p - ch;
-    int cxq = ch;
-    bool done = reading == 1 && rem == 0;
-    int kk = 0;
-    while (!done) {
-      if (kk >= K) {   // cannot happen for p <= max_prompt; guard the tail bounds
-        set_error(err, kErrIter);
-        E = __builtin_nan("");
-        break;
-      }
-      const int Dk = kk == 0 ? D1 : tr.tailD[(int64_t)kk * ZI + qid];
-      const int64_t Ck = kk == 0 ? C1 : tr.tailC[(int64_t)kk * ZI + qid];
-      if (rem > 0) {
-        const int room = k.B - Dk;
-        const int c2 = rem < room ? rem : room;
-        E = __dadd_rn(E, bt_ca(bt_pd(c2, Dk), Ck,
-                               need_A ? (int64_t)c2 * cxq + (int64_t)c2 * (c2 + 1) / 2 : 0));
-        rem -= c2;
-        cxq += c2;
-        done = reading == 1 && rem == 0;
-      } else {
-        E = __dadd_rn(E, bt_ca(bt_pd(0, Dk + 1), Ck + cxq, 0));
-        done = true;
-      }
-      ++kk;
-      ++it;
-    }
-    if (it > max_iters) set_error(err, kErrIter);
-    ttft[o] = __dsub_rn(E, t);
-    if (iters) iters[o] = (int32_t)it;
+    int32_t it;
+    ttft[o] = b.query(tr, qid, ZI, s_p[q - q0], t, max_prompt, reading, max_iters, err, &it);
+    if (iters) iters[o] = it;
   }
 }
 
@@ -251,49 +309,13 @@ __global__ __launch_bounds__(256) void k_route(int Z, int Q, int I, const double
   const int z = row / Q;
   const int q = row % Q;
   const double wc = w_cost[z];
-  const double wl = w_lat[z];
   const double* trow = ttft + (int64_t)z * ttft_zstride + (int64_t)q * I;
   const double* arow = acc + (int64_t)q * n_cols;
   const double* crow = cost + (int64_t)q * n_cols;
-  const double tq = tau ? tau[q] : 0.0;
-  double bu = 0.0;
-  int bj = -1;
-  // four instances per lane and pass, their loads issued before any is used
-  for (int j0 = lane_id(); j0 < I; j0 += 4 * kWave) {
-    int cc[4];
-    double tt[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = j0 + u * kWave;
-      cc[u] = j < I ? col[j] : 0;
-      tt[u] = j < I ? trow[j] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = j0 + u * kWave;
-      if (j < I) {
-        const double eq2 = __dsub_rn(arow[cc[u]], __dmul_rn(wc, crow[cc[u]]));
-        int k;
-        const double v = cand_value(eq2, tt[u], wl, tau, tq, j, &k);
-        if (better(v, k, bu, bj)) { bu = v; bj = k; }
-      }
-    }
-  }
-  // the row's best over the lanes (DPP; `better` is a total order, so the combining
-  // order does not matter)
-  lane_best(bu, bj, kWave);
+  const int bj = row_best(I, trow, arow, crow, col, wc, w_lat[z], tau, tau ? tau[q] : 0.0);
   if (lane_id() == 0) {
     const int64_t o = (int64_t)z * out_zstride + out_q0 + q;
-    bj = bj >= 0 ? key_index(bj) : -1;
-    if (bj < 0) set_error(err, kErrArg);   // no instance can take the query
-    choice[o] = bj;
-    if (bj >= 0) {
-      if (chosen_ttft) chosen_ttft[o] = trow[bj];
-      if (utility) {
-        const int c = col[bj];
-        utility[o] = __dsub_rn(arow[c], __dmul_rn(wc, crow[c]));
-      }
-    }
+    row_outputs(bj, o, trow, arow, crow, col, wc, choice, chosen_ttft, utility, err);
   }
 }
 
@@ -395,13 +417,16 @@ __device__ __forceinline__ void drain(Queue<KS> w, const QEnv& e, const int32_t*
   }
 }
 
-template <int KS>
+// STEP: the row of the query's estimates is routed here too.  Every wave of a scenario
+// finds the same winner from the row (24 bytes per instance, in cache), so the route
+// needs no launch of its own; the scenario's first wave writes the outputs.
+template <int KS, bool STEP>
 __global__ __launch_bounds__(kWave) void k_commit(DevState S, DevParams pr, int Z, int I,
                                                  const int32_t* choice, int64_t choice_zstride,
                                                  const int32_t* qp_ptr, const int32_t* qd_ptr,
                                                  int32_t qp_val, int32_t qd_val,
                                                  const double* t_ptr, double t_val,
-                                                 int64_t max_iters, int32_t* err) {
+                                                 int64_t max_iters, int32_t* err, StepRow sr) {
   const int qid = blockIdx.x;
   if (qid >= Z * I) return;
   const int z = qid / I;
@@ -411,7 +436,9 @@ __global__ __launch_bounds__(kWave) void k_commit(DevState S, DevParams pr, int 
   const QEnv e = make_env(S, pr, qid, j, stage);
   Queue<KS> w;
   w.load(S, e, qid);
-  const bool chosen = choice && choice[(int64_t)z * choice_zstride] == j;
+  bool chosen;
+  if constexpr (STEP) chosen = step_route(sr, I, z, j, pr.col, err) == j;
+  else chosen = choice && choice[(int64_t)z * choice_zstride] == j;
   const int p = qp_ptr ? *qp_ptr : qp_val;
   const int d = qd_ptr ? *qd_ptr : qd_val;
   const Track off{nullptr, 0, 0, 0};
@@ -1754,14 +1781,17 @@ __global__ __launch_bounds__(256) void k_ontime(int N, int I, const int32_t* cho
 __global__ void k_clear_error(int32_t* err) { *err = 0; }
 
 // ------------------------------------------------------------------ launchers
-template <int KS>
-static hipError_t launch_traj_ks(const LaunchEnv& env, const double* t_ptr, double t_val) {
+template <int KS, bool STEP>
+static hipError_t launch_traj_ks(const LaunchEnv& env, const double* t_ptr, double t_val,
+                                 const StepQuery& sq) {
   if (env.no_ctx_term)
-    hipLaunchKernelGGL((k_traj<KS, false>), dim3(env.Z * env.I), dim3(kWave), 0, env.stream,
-                       env.S, env.P, env.T, env.Z, env.I, t_ptr, t_val, env.max_iters, env.err);
+    hipLaunchKernelGGL((k_traj<KS, false, STEP>), dim3(env.Z * env.I), dim3(kWave), 0,
+                       env.stream, env.S, env.P, env.T, env.Z, env.I, t_ptr, t_val,
+                       env.max_iters, env.err, sq);
   else
-    hipLaunchKernelGGL((k_traj<KS, true>), dim3(env.Z * env.I), dim3(kWave), 0, env.stream,
-                       env.S, env.P, env.T, env.Z, env.I, t_ptr, t_val, env.max_iters, env.err);
+    hipLaunchKernelGGL((k_traj<KS, true, STEP>), dim3(env.Z * env.I), dim3(kWave), 0,
+                       env.stream, env.S, env.P, env.T, env.Z, env.I, t_ptr, t_val,
+                       env.max_iters, env.err, sq);
   return hipGetLastError();
 }
 
@@ -1770,9 +1800,20 @@ static hipError_t launch_commit_ks(const LaunchEnv& env, const int32_t* choice,
                                    int64_t choice_zstride, const int32_t* qp_ptr,
                                    const int32_t* qd_ptr, int32_t qp, int32_t qd,
                                    const double* t_ptr, double t_val) {
-  hipLaunchKernelGGL(k_commit<KS>, dim3(env.Z * env.I), dim3(kWave), 0, env.stream, env.S,
-                     env.P, env.Z, env.I, choice, choice_zstride, qp_ptr, qd_ptr, qp, qd, t_ptr,
-                     t_val, env.max_iters, env.err);
+  hipLaunchKernelGGL((k_commit<KS, false>), dim3(env.Z * env.I), dim3(kWave), 0, env.stream,
+                     env.S, env.P, env.Z, env.I, choice, choice_zstride, qp_ptr, qd_ptr, qp, qd,
+                     t_ptr, t_val, env.max_iters, env.err, StepRow{});
+  return hipGetLastError();
+}
+
+template <int KS>
+static hipError_t launch_step_ks(const LaunchEnv& env, const StepArgs& a, const StepRow& sr) {
+  const hipError_t e = launch_traj_ks<KS, true>(
+      env, a.t, 0.0, StepQuery{a.qp, env.max_prompt, env.reading, a.row_ttft});
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_commit<KS, true>), dim3(env.Z * env.I), dim3(kWave), 0, env.stream,
+                     env.S, env.P, env.Z, env.I, nullptr, 0, a.qp, a.qd, 0, 0, a.t_next, 0.0,
+                     env.max_iters, env.err, sr);
   return hipGetLastError();
 }
 
@@ -1954,12 +1995,13 @@ hipError_t launch_trace(const LaunchEnv& env, const TraceArgs& a) {
 
 hipError_t launch_traj(const LaunchEnv& env, const double* t_ptr, double t_val) {
   if (env.limited) return hipSuccess;   // estimates under limits simulate from the state
+  const StepQuery none{};
   switch (env.ks) {
-    case 1: return launch_traj_ks<1>(env, t_ptr, t_val);
-    case 2: return launch_traj_ks<2>(env, t_ptr, t_val);
-    case 4: return launch_traj_ks<4>(env, t_ptr, t_val);
-    case 8: return launch_traj_ks<8>(env, t_ptr, t_val);
-    case 16: return launch_traj_ks<16>(env, t_ptr, t_val);
+    case 1: return launch_traj_ks<1, false>(env, t_ptr, t_val, none);
+    case 2: return launch_traj_ks<2, false>(env, t_ptr, t_val, none);
+    case 4: return launch_traj_ks<4, false>(env, t_ptr, t_val, none);
+    case 8: return launch_traj_ks<8, false>(env, t_ptr, t_val, none);
+    case 16: return launch_traj_ks<16, false>(env, t_ptr, t_val, none);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1979,17 +2021,39 @@ hipError_t launch_commit(const LaunchEnv& env, const int32_t* choice, int64_t ch
   }
 }
 
+hipError_t launch_step(const LaunchEnv& env, const StepArgs& a) {
+  const StepRow sr{a.row_ttft, a.acc, a.cost, a.w_cost, a.w_lat, a.tau, a.choice,
+                   a.chosen_ttft, a.utility};
+  if (env.limited) {
+    const hipError_t e = launch_lim_est(env, 1, a.qp, a.t, 0.0, a.row_ttft, nullptr);
+    return e == hipSuccess ? launch_lim_step_commit(env, a, sr) : e;
+  }
+  switch (env.ks) {
+    case 1: return launch_step_ks<1>(env, a, sr);
+    case 2: return launch_step_ks<2>(env, a, sr);
+    case 4: return launch_step_ks<4>(env, a, sr);
+    case 8: return launch_step_ks<8>(env, a, sr);
+    case 16: return launch_step_ks<16>(env, a, sr);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_est(const LaunchEnv& env, int Q, const int32_t* q_prefill, const double* t_ptr,
                       double t_val, double* ttft, int32_t* iters) {
   if (env.limited) return launch_lim_est(env, Q, q_prefill, t_ptr, t_val, ttft, iters);
-  const int64_t blocks =
-      (int64_t)env.Z * ((Q + kEstChunk - 1) / kEstChunk) * ((env.I + 255) / 256);
+  const int64_t cols = (int64_t)env.Z * ((env.I + 255) / 256);
+  // Queries per block: as many as kEstChunk (the instance's background is loaded once
+  // for them) while the blocks still give every CU two; a thread's queries run one
+  // after another, so a small call takes a shorter chunk and more blocks: 29 queries x 37
+  // instances 10.8 us with chunks of 16 (2 blocks), 4.7 with chunks of 1.
+  int64_t chunk = ((int64_t)Q * cols + 511) / 512;
+  chunk = chunk < 1 ? 1 : (chunk > kEstChunk ? kEstChunk : chunk);
+  const int64_t blocks = cols * ((Q + chunk - 1) / chunk);
   if (blocks == 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_est, dim3((unsigned)blocks), dim3(256), 0, env.stream, env.P, env.T,
-                     env.Z, Q, env.I, q_prefill, t_ptr, t_val, env.max_prompt, env.reading,
-                     env.max_iters,
-                     ttft, iters, env.err);
+                     env.Z, Q, env.I, (int)chunk, q_prefill, t_ptr, t_val, env.max_prompt,
+                     env.reading, env.max_iters, ttft, iters, env.err);
   return hipGetLastError();
 }
 

@@ -59,6 +59,27 @@ struct TraceArgs {
   int tag0;            // tag of query 0 in the ring (queries tag0 .. tag0 + N - 1)
 };
 
+// One routing step (lar_route_step): the query's values and the outputs in device memory.
+struct StepArgs {
+  const int32_t *qp, *qd;
+  const double *t, *t_next;
+  double* row_ttft;    // [Z][I] workspace: the query's estimates
+  const double *acc, *cost;
+  const double *w_cost, *w_lat, *tau;
+  int32_t* choice;
+  double *chosen_ttft, *utility;
+};
+
+// What the route inside a step's commit kernel reads and writes.
+struct StepRow {
+  const double *ttft, *acc, *cost;
+  const double *w_cost, *w_lat, *tau;
+  int32_t* choice;
+  double *chosen_ttft, *utility;
+};
+
+hipError_t launch_step(const LaunchEnv& env, const StepArgs& a);
+hipError_t launch_lim_step_commit(const LaunchEnv& env, const StepArgs& a, const StepRow& sr);
 hipError_t launch_trace(const LaunchEnv& env, const TraceArgs& a);
 hipError_t launch_traj(const LaunchEnv& env, const double* t_ptr, double t_val);
 hipError_t launch_est(const LaunchEnv& env, int Q, const int32_t* q_prefill, const double* t_ptr,

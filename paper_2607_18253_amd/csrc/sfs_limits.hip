@@ -162,13 +162,15 @@ __global__ __launch_bounds__(kWave) void k_lest(DevState S, DevParams pr, DevLim
   }
 }
 
-template <int KS>
+// STEP: the row of the query's estimates is routed here too (see k_commit).
+template <int KS, bool STEP>
 __global__ __launch_bounds__(kWave) void k_lcommit(DevState S, DevParams pr, DevLimits lm, int Z,
                                                   int I, const int32_t* choice,
                                                   int64_t choice_zstride, const int32_t* qp_ptr,
                                                   const int32_t* qd_ptr, int32_t qp_val,
                                                   int32_t qd_val, const double* t_ptr,
-                                                  double t_val, int64_t max_iters, int32_t* err) {
+                                                  double t_val, int64_t max_iters, int32_t* err,
+                                                  StepRow sr) {
   const int qid = blockIdx.x;
   if (qid >= Z * I) return;
   const int z = qid / I;
@@ -178,7 +180,9 @@ __global__ __launch_bounds__(kWave) void k_lcommit(DevState S, DevParams pr, Dev
   const LEnv e = make_lenv(S, pr, lm, qid, j, lds);
   LQueue<KS> w;
   w.template load<false>(S, e, qid, nullptr);
-  const bool chosen = choice && choice[(int64_t)z * choice_zstride] == j;
+  bool chosen;
+  if constexpr (STEP) chosen = step_route(sr, I, z, j, pr.col, err) == j;
+  else chosen = choice && choice[(int64_t)z * choice_zstride] == j;
   const int p = qp_ptr ? *qp_ptr : qp_val;
   const int d = qd_ptr ? *qd_ptr : qd_val;
   const LTrack off{nullptr, 0, 0, 0};
@@ -452,10 +456,18 @@ hipError_t launch_lim_commit(const LaunchEnv& env, const int32_t* choice,
                                     int64_t choice_zstride, const int32_t* qp_ptr,
                                     const int32_t* qd_ptr, int32_t qp, int32_t qd,
                                     const double* t_ptr, double t_val) {
-  LIM_SWITCH(KSV, hipLaunchKernelGGL(k_lcommit<KSV>, dim3(env.Z * env.I), dim3(kWave), 0,
-                                     env.stream, env.S, env.P, env.L, env.Z, env.I, choice,
-                                     choice_zstride, qp_ptr, qd_ptr, qp, qd, t_ptr, t_val,
-                                     env.max_iters, env.err))
+  LIM_SWITCH(KSV, hipLaunchKernelGGL((k_lcommit<KSV, false>), dim3(env.Z * env.I),
+                                     dim3(kWave), 0, env.stream, env.S, env.P, env.L, env.Z,
+                                     env.I, choice, choice_zstride, qp_ptr, qd_ptr, qp, qd,
+                                     t_ptr, t_val, env.max_iters, env.err, StepRow{}))
+  return hipGetLastError();
+}
+
+hipError_t launch_lim_step_commit(const LaunchEnv& env, const StepArgs& a, const StepRow& sr) {
+  LIM_SWITCH(KSV, hipLaunchKernelGGL((k_lcommit<KSV, true>), dim3(env.Z * env.I), dim3(kWave),
+                                     0, env.stream, env.S, env.P, env.L, env.Z, env.I, nullptr,
+                                     0, a.qp, a.qd, 0, 0, a.t_next, 0.0, env.max_iters, env.err,
+                                     sr))
   return hipGetLastError();
 }
 

@@ -100,6 +100,71 @@ __device__ __forceinline__ void lane_best(double& u, int& j, int n) {
   j = __builtin_amdgcn_readlane(j, src);
 }
 
+// The winner of one row: the key of the best of instances 0 .. I - 1 (-1: none),
+// wave-uniform.  trow: their estimates, arow / crow: the query's accuracy and cost.
+__device__ __forceinline__ int row_best(int I, const double* trow, const double* arow,
+                                        const double* crow, const int32_t* col, double wc,
+                                        double wl, const double* tau, double tq) {
+  double bu = 0.0;
+  int bj = -1;
+  // four instances per lane and pass, their loads issued before any is used
+  for (int j0 = lane_id(); j0 < I; j0 += 4 * kWave) {
+    int cc[4];
+    double tt[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = j0 + u * kWave;
+      cc[u] = j < I ? col[j] : 0;
+      tt[u] = j < I ? trow[j] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = j0 + u * kWave;
+      if (j < I) {
+        const double eq2 = __dsub_rn(arow[cc[u]], __dmul_rn(wc, crow[cc[u]]));
+        int k;
+        const double v = cand_value(eq2, tt[u], wl, tau, tq, j, &k);
+        if (better(v, k, bu, bj)) { bu = v; bj = k; }
+      }
+    }
+  }
+  // the row's best over the lanes (DPP; `better` is a total order, so the combining
+  // order does not matter)
+  lane_best(bu, bj, kWave);
+  return bj;
+}
+
+// A routed row's outputs at index o (one lane).  bj: row_best's key.
+__device__ __forceinline__ void row_outputs(int bj, int64_t o, const double* trow,
+                                            const double* arow, const double* crow,
+                                            const int32_t* col, double wc, int32_t* choice,
+                                            double* chosen_ttft, double* utility,
+                                            int32_t* err) {
+  bj = bj >= 0 ? key_index(bj) : -1;
+  if (bj < 0) set_error(err, kErrArg);   // no instance can take the query
+  choice[o] = bj;
+  if (bj >= 0) {
+    if (chosen_ttft) chosen_ttft[o] = trow[bj];
+    if (utility) {
+      const int c = col[bj];
+      utility[o] = __dsub_rn(arow[c], __dmul_rn(wc, crow[c]));
+    }
+  }
+}
+
+// A routing step's route inside its commit kernel, in the wave of scenario z's instance
+// j: the chosen instance (-1: none); instance 0's wave writes the outputs.
+__device__ __forceinline__ int step_route(const StepRow& s, int I, int z, int j,
+                                          const int32_t* col, int32_t* err) {
+  const double wc = s.w_cost[z];
+  const double* trow = s.ttft + (int64_t)z * I;
+  const int bj = row_best(I, trow, s.acc, s.cost, col, wc, s.w_lat[z], s.tau,
+                          s.tau ? s.tau[0] : 0.0);
+  if (j == 0 && lane_id() == 0)
+    row_outputs(bj, z, trow, s.acc, s.cost, col, wc, s.choice, s.chosen_ttft, s.utility, err);
+  return bj >= 0 ? key_index(bj) : -1;
+}
+
 // Trace inputs of one query, loaded one query ahead so their memory latency hides
 // behind the previous query's work.  Lane l of a wave holds acc / cost of the wave's
 // l-th owned instance.
