@@ -21,10 +21,17 @@
 // kept in arrival order, running requests first.  Its first KS*64 entries (KS*64 >= M,
 // so every entry a batch can touch) sit in registers, list position s*64 + lane in
 // slot s; the rest stay in the queue's HBM ring at index (head + position) mod rcap.
-// A batch is composed in parallel (saturating DPP prefix sums for the chunks, a
-// block-count test, a prefix rule for the admissions); only a batch that must
-// preempt is composed by one lane, step by step, over an LDS copy of the running
-// requests.
+// A batch's decode tokens and new blocks are counted by ballots; the blocks held and
+// the context of the decoding requests are carried from batch to batch.  The chunks
+// and admissions go to the few requests that get budget, one by one in list order on
+// the scalar unit (kSerialMax of them; past that by saturating DPP prefix sums and a
+// prefix rule), and a batch that must preempt pops its victims the same way.  Batches
+// that repeat the one before are folded (LQueue::fold).  One wave per SIMD runs at the
+// latency of its dependent instructions, so their number is the engine's time: about
+// 770 a batch where a full KV cache preempts.  Against wave sums for every count, prefix
+// sums over every row and one lane walking lists in LDS to preempt (and without the
+// shared and carried admission points of sfs_limits.hip): 27 instances x 243 queries 504 -> 338 us, 32
+// instances, 6000 queries 158 -> 127 ms.
 #pragma once
 
 #include "sfs_device.h"
@@ -37,10 +44,28 @@ struct DevLimits {
   const int32_t *H, *K, *sh, *X;
 };
 
-// LDS words per wave of the limits engine: five rows of KS*64 (compaction staging,
-// or the serial batch's working copy) and a few scalars.
+// LDS words per wave of the limits engine: five rows of KS*64 (compaction staging).
 template <int KS>
-constexpr int lim_lds_words() { return 5 * KS * kWave + 4; }
+constexpr int lim_lds_words() { return 5 * KS * kWave; }
+
+// Requests that one stage of a batch (the partial prefills, then the admissions) serves
+// one by one: each takes about 30 scalar instructions, about as many as one row of
+// prefix sums, and the requests of one stage usually sit in one or two rows.
+constexpr int kSerialMax = 3;
+
+// Admission point of each queue for the queries of one what-if call: the window
+// (three rows of cap entries per queue) and the scalars.
+struct LFront {
+  int ok;      // 0: no admission point (the estimates start from the state)
+  int nwin, n_list, n_run, head, held;
+  int64_t csum, pre;   // pre: batches folded into clock
+  double clock;
+};
+struct DevFront {
+  int32_t* win;    // [ZI][3][cap]; nullptr: no workspace
+  LFront* sc;      // [ZI]
+  int cap;
+};
 
 struct LEnv {
   Coef k;
@@ -73,8 +98,9 @@ __device__ __forceinline__ LEnv make_lenv(const DevState& S, const DevParams& pr
 }
 
 // Blocks that hold x cached tokens.
+// (x < 2^31 and a block is at most 65536 tokens, so the sum fits 32 unsigned bits.)
 __device__ __forceinline__ int kv_blocks(int x, int sh) {
-  return (int)(((int64_t)x + (1 << sh) - 1) >> sh);
+  return (int)(((uint32_t)x + (1u << sh) - 1u) >> sh);
 }
 
 // Predicted decode of a request entering with p prompt tokens: >= 1, cut to what the
@@ -99,7 +125,12 @@ struct LStep {
   bool last_dec;   // the last list entry received a decode token
   bool last_fill;  // the last list entry's prefill completed
   bool tail_ok;    // (TAIL steps) a new request at the tail could have been admitted
+  bool same;       // the next batch serves the same requests the same tokens, unless a
+                   // decoding request finishes in it or the KV cache runs short
+  int P, D, np;    // prefill and decode tokens, requests with a chunk
+  int64_t C, A, gg;  // context and attention features, sum of the squared chunks
 };
+
 
 template <int KS>
 struct LQueue {
@@ -110,6 +141,9 @@ struct LQueue {
   int head;      // ring index of list position 0
   int next_seq;
   int ntrk;      // tracked queries without a first token (tracking replays)
+  int held;      // KV blocks of the running requests (K > 0)
+  int64_t csum;  // context of the decoding requests (d != 0)
+  int nfin;      // batches to the first finish of a decoding request; 0: not known
   double clock;
   int64_t iters;
   // a query appended by an estimate to its private copy is written nowhere: while it
@@ -157,6 +191,24 @@ struct LQueue {
 #pragma unroll
     for (int s = 0; s < KS; ++s) { rp[s] = 0; rd[s] = 0; cx[s] = 0; sq[s] = 0; tg[s] = -1; }
     refill<TRK>(e, tags);
+    recount(e);
+  }
+
+  // held, csum and nfin from the window (every running request is in it).
+  __device__ void recount(const LEnv& e) {
+    const int ln = lane_id();
+    int h = 0;
+    int64_t c = 0;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if (s * kWave + ln < n_run) {
+        h += kv_blocks(cx[s], e.sh);
+        if (rp[s] == 0) c += cx[s];
+      }
+    }
+    held = e.K > 0 ? wave_sum32(h) : 0;
+    csum = e.need_C ? wave_sum64(c) : 0;
+    nfin = 0;
   }
 
   template <bool TRK>
@@ -217,130 +269,181 @@ struct LQueue {
     next_seq += 1;
   }
 
-  // The batch when it must preempt, following the rule step by step on an LDS copy
-  // of the running requests.  Only three kinds of request can change the outcome: the
-  // decoding ones that need a new block (in list order), the partial prefills (in
-  // list order) and the victims (from the end); the wave lists the first two and one
-  // lane walks them.  Every other decoding request is served exactly when it is still
-  // running after the walk.  On return dec / chk hold the tokens of each running
-  // request, the victims are waiting again (rp, cx updated) and n_run is the new
-  // running count.  Admissions do not happen in such a batch.
-  __device__ void compose_serial(const LEnv& e, int free0, int (&dec)[KS], int (&chk)[KS]) {
+  // Copy to / from a what-if's admission point (a private copy: no arrival numbers).
+  __device__ void to_front(const DevFront& f, int qid, int ok, int64_t pre) const {
     const int ln = lane_id();
-    const int sh = e.sh;
-    int* Lrp = e.lds;
-    int* Lcx = Lrp + KS * kWave;
-    int* Lch = Lcx + KS * kWave;
-    int* Lnd = Lch + KS * kWave;   // positions of the decoding requests that need a block
-    int* Lpt = Lnd + KS * kWave;   // positions of the partial prefills
-    int* Lsc = Lpt + KS * kWave;
-    int nn = 0, np = 0, ndec = 0;
+    int32_t* w = f.win + (int64_t)qid * 3 * f.cap;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const int i = s * kWave + ln;
-      const bool run = i < n_run;
-      if (run) { Lrp[i] = rp[s]; Lcx[i] = cx[s]; Lch[i] = 0; }
-      const bool isdec = run && rp[s] == 0;
-      const bool needy = isdec && kv_blocks(cx[s] + 1, sh) > kv_blocks(cx[s], sh);
-      const bool part = run && rp[s] > 0;
-      const uint64_t mn = ballot(needy), mp = ballot(part);
-      if (needy) Lnd[nn + mbcnt(mn)] = i;
-      if (part) Lpt[np + mbcnt(mp)] = i;
-      nn += popc(mn);
-      np += popc(mp);
-      ndec += popc(ballot(isdec));
+      const int x = s * kWave + ln;
+      if (x < nwin) { w[x] = rp[s]; w[f.cap + x] = rd[s]; w[2 * f.cap + x] = cx[s]; }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (ln == 0) {
-      int run = n_run, freeb = free0, dvict = 0;
-      // decode tokens: each decoding request that needs a block takes one, preempting
-      // from the end while none is free
-      for (int k = 0; k < nn; ++k) {
-        const int r = Lnd[k];
-        while (freeb < 1 && r < run) {
-          const int v = run - 1;
-          const int rv = Lrp[v], cv = Lcx[v];
-          freeb += kv_blocks(cv, sh);
-          dvict += rv == 0 ? 1 : 0;
-          Lrp[v] = rv + cv;
-          Lcx[v] = 0;
-          run = v;
-        }
-        if (r >= run) break;
-        freeb -= 1;
-      }
-      const int run1 = run;   // decoding requests below run1 hold a decode token
-      int left = e.k.B - (ndec - dvict);
-      // chunks of the partial prefills; a victim that decodes in this batch returns
-      // its token and the block it took for it
-      for (int k = 0; k < np; ++k) {
-        const int r = Lpt[k];
-        if (r >= run || left == 0) break;
-        const int g = min(min(Lrp[r], e.H), left);
-        const int cr = Lcx[r];
-        const int need = kv_blocks(cr + g, sh) - kv_blocks(cr, sh);
-        while (freeb < need && r < run) {
-          const int v = run - 1;
-          const int rv = Lrp[v], cv = Lcx[v];
-          if (rv == 0 && v < run1) {
-            freeb += kv_blocks(cv + 1, sh);
-            left += 1;
-          } else {
-            freeb += kv_blocks(cv, sh);
-          }
-          Lrp[v] = rv + cv;
-          Lcx[v] = 0;
-          run = v;
-        }
-        if (r >= run) break;
-        Lch[r] = g;
-        freeb -= need;
-        left -= g;
-      }
-      Lsc[0] = run;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int run_end = uni(Lsc[0]);
+    if (ln == 0) f.sc[qid] = LFront{ok, nwin, n_list, n_run, head, held, csum, pre, clock};
+  }
+  __device__ void from_front(const DevFront& f, int qid) {
+    const int ln = lane_id();
+    const LFront* q = f.sc + qid;
+    nwin = uni(q->nwin); n_list = uni(q->n_list); n_run = uni(q->n_run); head = uni(q->head);
+    held = uni(q->held); csum = uni64(q->csum); clock = q->clock;
+    nfin = 0; next_seq = 0; ntrk = 0; iters = 0;
+    vq = false; vq_p = 0; vq_d = 0;
+    const int32_t* w = f.win + (int64_t)qid * 3 * f.cap;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const int i = s * kWave + ln;
-      if (i < n_run) {
-        const bool isdec = rp[s] == 0;
-        dec[s] = (isdec && i < run_end) ? 1 : 0;
-        chk[s] = (!isdec && i < run_end) ? Lch[i] : 0;
-        rp[s] = Lrp[i];
-        cx[s] = Lcx[i];
-      }
+      const int x = s * kWave + ln;
+      const bool v = x < nwin;
+      rp[s] = v ? w[x] : 0;
+      rd[s] = v ? w[f.cap + x] : 0;
+      cx[s] = v ? w[2 * f.cap + x] : 0;
+      sq[s] = 0; tg[s] = -1;
     }
-    n_run = run_end;
-    // the LDS area is reused by the next batch
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 
-  // Remove the finished window entries (fin[s] on this lane), keeping the order, and
-  // refill the window from the ring.
-  template <bool TRK>
-  __device__ void compact(const LEnv& e, const int32_t* tags, const bool (&fin)[KS], int nf) {
+  // A private copy takes the request that the live queue has just appended: into the
+  // window when it is that long; else the ring slot already holds it (a copy ahead of
+  // its queue has as many requests fewer as its head is further).
+  __device__ void join(int p, int d) {
+    const int ln = lane_id();
+    const int pos = n_list;
+    if (nwin == n_list && pos < KS * kWave) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+        if (s * kWave + ln == pos) { rp[s] = p; rd[s] = d; cx[s] = 0; }
+      nwin = pos + 1;
+    }
+    n_list += 1;
+    next_seq += 1;
+  }
+
+  // The batch when it must preempt.  dm: the decoding requests, nm: those that need a
+  // new block, per row; free0: free blocks; D: their number.
+  //
+  // Decode tokens go in list order, and the victim is always the last running request,
+  // so no request that has its token is a victim of this stage: the victims are the
+  // fewest last ones whose blocks, with the free ones, give every remaining request
+  // that needs a block one.  Then the partial prefills in list order, each popping
+  // victims until its blocks fit or it is out itself; a victim that holds a decode
+  // token of this batch returns it and the block it took.  On return chk holds the
+  // chunks, n_run the new running count, D and P the tokens, cfill the context of the
+  // requests whose prefill completes; the victims are waiting again (rp, cx updated).
+  // Admissions do not happen in such a batch.  Returns the free blocks.
+  __device__ __forceinline__ int compose_preempt(const LEnv& e, const uint64_t (&dm)[KS],
+                                                 const uint64_t (&nm)[KS], int free0,
+                                                 int (&chk)[KS], int& D, int& P, int& fillc,
+                                                 int64_t& cfill, int& lf) {
+    const int ln = lane_id();
+    const int sh = e.sh;
+    const int run0 = n_run;
+    int run = n_run, freeb = free0, nn = 0;
+    int hb[KS];   // blocks held
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      nn += popc(nm[s]);
+      hb[s] = kv_blocks(cx[s], sh);
+    }
+    // the row of the last running request, kept while victims are popped from it
+    int v_row = -1, v_hb = 0;
+    uint64_t v_dm = 0, v_nm = 0;
+    auto pop = [&]() {
+      run -= 1;
+      if ((run >> 6) != v_row) {
+        v_row = run >> 6;
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+          if (k == v_row) { v_hb = hb[k]; v_dm = dm[k]; v_nm = nm[k]; }
+      }
+      return run & (kWave - 1);
+    };
+    while (freeb < nn) {   // (a pass pops one request; with none left nn is 0)
+      const int vl = pop();
+      freeb += lane_read(v_hb, vl);
+      nn -= (int)((v_nm >> vl) & 1);
+      D -= (int)((v_dm >> vl) & 1);
+    }
+    freeb -= nn;
+    int left = e.k.B - D;
+    P = 0;
+    fillc = 0;
+    cfill = 0;
+    lf = 0;
+#pragma unroll 1
+    for (int s = 0; s * kWave < run && left > 0; ++s) {
+      uint64_t md = 0;
+      int r_rp = 0, r_cx = 0, r_hb = 0;
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+        if (k == s) { md = dm[k]; r_rp = rp[k]; r_cx = cx[k]; r_hb = hb[k]; }
+      uint64_t m = ballot(s * kWave + ln < run) & ~md;   // partial prefills of this row
+      if (m == 0) continue;
+      const int r_w = min(r_rp, e.H);
+      const int r_nb = kv_blocks(r_cx + r_w, sh) - r_hb;
+      int r_ch = 0;
+      while (m) {
+        const int l = __builtin_ctzll(m);
+        m &= m - 1;
+        const int r = s * kWave + l;
+        int g = lane_read(r_w, l);
+        int need = lane_read(r_nb, l);
+        if (g > left) {
+          g = left;
+          need = kv_blocks(lane_read(r_cx, l) + g, sh) - lane_read(r_hb, l);
+        }
+        while (freeb < need && r < run) {
+          const int vl = pop();
+          const int tok = (int)((v_dm >> vl) & 1);
+          freeb += lane_read(v_hb, vl) + (int)((v_nm >> vl) & 1);
+          left += tok;
+          D -= tok;
+        }
+        if (r >= run) break;
+        r_ch = ln == l ? g : r_ch;
+        freeb -= need;
+        left -= g;
+        P += g;
+        if (left == 0) break;
+      }
+      const uint64_t mf = ballot(r_ch > 0 && r_ch == r_rp);
+      fillc += popc(mf);
+      if (e.need_C) cfill += sum_lanes64(r_cx + r_ch, mf);
+      if ((n_list - 1) >> 6 == s) lf = (int)((mf >> ((n_list - 1) & (kWave - 1))) & 1);
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+        if (k == s) chk[k] = r_ch;
+    }
+    n_run = run;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int i = s * kWave + ln;
+      if (i >= run && i < run0) { rp[s] += cx[s]; cx[s] = 0; }
+    }
+    return freeb;
+  }
+
+  // Remove the finished window entries keeping the order, and
+  // refill the window from the ring.  fm: the finished ones per row.  LIVE: with the arrival numbers.
+  template <bool TRK, bool LIVE>
+  __device__ void compact(const LEnv& e, const int32_t* tags, const uint64_t (&fm)[KS], int nf) {
     const int ln = lane_id();
     int* Srp = e.lds;
     int* Srd = Srp + KS * kWave;
     int* Scx = Srd + KS * kWave;
     int* Ssq = Scx + KS * kWave;
     int* Stg = Ssq + KS * kWave;
-    int base = 0;
+    // (rows before the first finished request stay as they are)
+    int first = KS - 1;
+#pragma unroll
+    for (int s = KS - 2; s >= 0; --s)
+      if (fm[s] != 0) first = s;
+    int base = first * kWave;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const bool keep = s * kWave + ln < nwin && !fin[s];
+      if (s < first) continue;
+      const bool keep = s * kWave + ln < nwin && !((fm[s] >> ln) & 1);
       const uint64_t m = ballot(keep);
       if (keep) {
         const int dst = base + mbcnt(m);
-        Srp[dst] = rp[s]; Srd[dst] = rd[s]; Scx[dst] = cx[s]; Ssq[dst] = sq[s];
+        Srp[dst] = rp[s]; Srd[dst] = rd[s]; Scx[dst] = cx[s];
+        if constexpr (LIVE) Ssq[dst] = sq[s];
         if constexpr (TRK) Stg[dst] = tg[s];
       }
       base += popc(m);
@@ -352,8 +455,9 @@ struct LQueue {
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int pos = s * kWave + ln;
-      if (pos < nw) {
-        rp[s] = Srp[pos]; rd[s] = Srd[pos]; cx[s] = Scx[pos]; sq[s] = Ssq[pos];
+      if (s >= first && pos < nw) {
+        rp[s] = Srp[pos]; rd[s] = Srd[pos]; cx[s] = Scx[pos];
+        if constexpr (LIVE) sq[s] = Ssq[pos];
         if constexpr (TRK) tg[s] = Stg[pos];
       }
     }
@@ -369,141 +473,242 @@ struct LQueue {
   }
 
   // One batch: compose, time, (TRK) first tokens at the batch end clk0 + T, apply.
-  // Only the window rows that hold entries are visited (wave-uniform row count), the
-  // chunk pass is skipped when no request has prefill left, and the admission pass
-  // when no request waits.  TAIL: also report whether a request appended at the tail
-  // before this batch could have been admitted in it -- no preemption, every waiting
-  // request admitted, a sequence slot, budget and a KV block left -- which every
-  // admission needs, whatever the request's prompt.
-  template <bool TRK, bool TAIL = false>
-  __device__ LStep step(const LEnv& e, const int32_t* tags, double clk0, const LTrack* tk) {
+  // Only the window rows that hold entries are visited (wave-uniform row count).
+  // LIVE: a live queue, not a private copy (of those, only an estimate's reports on the
+  // last list entry).  TAIL: also report whether a request
+  // appended at the tail before this batch could have been admitted in it -- no
+  // preemption, every waiting request admitted, a sequence slot, budget and a KV block
+  // left -- which every admission needs, whatever the request's prompt; if it could,
+  // the batch is not applied.  chk receives each entry's chunk.
+  template <bool TRK, bool LIVE, bool TAIL>
+  __device__ __forceinline__ LStep step(const LEnv& e, const int32_t* tags, double clk0,
+                                        const LTrack* tk, int (&chk)[KS]) {
+    constexpr bool EST = !LIVE && !TAIL;   // an estimate: reports on the last list entry
     const int ln = lane_id();
     const int sh = e.sh;
     const bool kv = e.K > 0;
     const int B = e.k.B, M = e.k.M;
     const int nrows = (nwin + kWave - 1) >> 6;
-    int dec[KS], chk[KS];
-    bool wait[KS];
-    // decoding requests, their new blocks, the blocks held
-    int nd = 0, held = 0, need = 0;
+    const int lp = n_list - 1;
+    // decoding requests and those of them that need a new block: the ones whose blocks
+    // are full
+    uint64_t dm[KS], nm[KS];
+    int D = 0, need = 0;
+    const int smask = (1 << sh) - 1;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      dec[s] = 0; chk[s] = 0; wait[s] = false;
+      dm[s] = 0; nm[s] = 0; chk[s] = 0;
       if (s < nrows) {
-        const int i = s * kWave + ln;
-        const bool run = i < n_run;
-        dec[s] = (run && rp[s] == 0) ? 1 : 0;
-        nd += dec[s];
-        if (kv && run) {
-          const int h = kv_blocks(cx[s], sh);
-          held += h;
-          if (dec[s]) need += kv_blocks(cx[s] + 1, sh) - h;
+        dm[s] = ballot(s * kWave + ln < n_run && rp[s] == 0);
+        D += popc(dm[s]);
+        if (kv) {
+          nm[s] = dm[s] & ballot((cx[s] & smask) == 0);
+          need += popc(nm[s]);
         }
       }
     }
-    int D = wave_sum32(nd);
     const int L1 = B - D;
-    const bool waiting_any = n_list > n_run;
-    const bool prefill_any = waiting_any || n_run > D;
-    // chunks: each partial prefill, then each waiting request within the sequence
-    // cap, wants min(rp, H); the budget left after the decodes goes to them in list
-    // order (exclusive saturating prefix sums, row by row)
-    if (prefill_any) {
-      unsigned carry = 0;
+    int left = L1;
+    // chunks of the partial prefills, in list order: min(rp, H, budget left).  When the
+    // decode tokens alone run out of blocks the preempting pass gives them.
+    const int room0 = kv ? e.K - held : 0;   // free blocks
+    int preempted = kv && need > room0 ? 1 : 0;
+    int P = 0, np = 0, fillc = 0;
+    int64_t A = 0, gg = 0, cfill = 0;
+    int same = 1, lf = 0;   // (ints: a bool across blocks would be a lane mask)
+    if (n_run > D && left > 0 && !preempted) {
+      int needp = 0;
+      if (n_run - D <= kSerialMax) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        if (s < nrows) {
-          const int i = s * kWave + ln;
-          const bool part = i < n_run && rp[s] > 0;
-          wait[s] = i >= n_run && i < nwin && i < M;
-          const int want = (part || wait[s]) ? min(min(rp[s], e.H), L1) : 0;
-          const unsigned excl =
-              min((unsigned)scan_sat(prev_lane(want), L1) + carry, (unsigned)L1);
-          chk[s] = min(want, L1 - (int)excl);
-          carry = (unsigned)uni(lane_last((int)min(excl + (unsigned)want, (unsigned)L1)));
-          if (kv && part) need += kv_blocks(cx[s] + chk[s], sh) - kv_blocks(cx[s], sh);
+        for (int s = 0; s < KS; ++s) {
+          if (s < nrows) {
+            uint64_t m = ballot(s * kWave + ln < n_run) & ~dm[s];
+            while (m && left > 0) {
+              const int l = __builtin_ctzll(m);
+              m &= m - 1;
+              const int r = lane_read(rp[s], l);
+              const int c = lane_read(cx[s], l);
+              const int g = min(min(r, e.H), left);
+              left -= g;
+              P += g;
+              np += 1;
+              chk[s] = ln == l ? g : chk[s];
+              needp += kv_blocks(c + g, sh) - kv_blocks(c, sh);
+              if (e.need_A) {
+                A += (int64_t)g * c + (int64_t)g * (g + 1) / 2;
+                gg += (int64_t)g * g;
+              }
+              if (r - g <= g) same = 0;
+              if (r == g) {
+                fillc += 1;
+                cfill += c + g;
+                if (EST && s * kWave + l == lp) lf = 1;
+              }
+            }
+          }
+        }
+      } else {
+        // exclusive saturating prefix sums, row by row where there are any
+        unsigned carry = 0;
+        int nd = 0;
+        int64_t a = 0, g2 = 0;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          if (s < nrows && carry < (unsigned)L1) {
+            const uint64_t pm = ballot(s * kWave + ln < n_run) & ~dm[s];
+            if (pm == 0) continue;
+            const int want = (pm >> ln) & 1 ? min(min(rp[s], e.H), L1) : 0;
+            const unsigned excl =
+                min((unsigned)scan_sat(prev_lane(want), L1) + carry, (unsigned)L1);
+            const int g = min(want, L1 - (int)excl);
+            chk[s] = g;
+            carry = (unsigned)uni(lane_last((int)min(excl + (unsigned)want, (unsigned)L1)));
+            if (kv) nd += kv_blocks(cx[s] + g, sh) - kv_blocks(cx[s], sh);
+            if (e.need_A) {
+              a += (int64_t)g * cx[s] + (int64_t)g * (g + 1) / 2;
+              g2 += (int64_t)g * g;
+            }
+            const uint64_t mf = ballot(g > 0 && g == rp[s]);
+            fillc += popc(mf);
+            np += popc(ballot(g > 0));
+            if (ballot(g > 0 && rp[s] - g <= g)) same = 0;
+            if (e.need_C) cfill += sum_lanes64(cx[s] + g, mf);
+            if (EST && s == (lp >> 6)) lf |= (int)((mf >> (lp & (kWave - 1))) & 1);
+          }
+        }
+        P = (int)carry;
+        left = L1 - P;
+        if (kv) needp = wave_sum32(nd);
+        if (e.need_A) {
+          A = wave_sum64(a);
+          gg = wave_sum64(g2);
         }
       }
+      if (kv && need + needp > room0) preempted = 1;
+      need += needp;
     }
-    bool preempted = false;
-    int room = 0;
-    if (kv) {
-      room = e.K - wave_sum32(held);    // free blocks
-      const int n12 = wave_sum32(need);
-      if (n12 > room) preempted = true;
-      room -= n12;
-    }
-    int admitted = 0;
+    int room = room0 - need;   // blocks free after the running requests' (K > 0)
+    int adm = 0;
     if (preempted) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) { dec[s] = 0; chk[s] = 0; }
-      compose_serial(e, room + wave_sum32(need), dec, chk);
-      int x = 0;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) x += dec[s];
-      D = wave_sum32(x);
-    } else if (waiting_any) {
-      // admissions: a prefix of the waiting requests, cut where the budget, the
-      // sequence cap or the blocks of a first chunk run out
-      int bcarry = 0, nadm = 0, nblk = 0;
+      for (int s = 0; s < KS; ++s) chk[s] = 0;
+      room = compose_preempt(e, dm, nm, room0, chk, D, P, fillc, cfill, lf);
+      same = 0;
+      int64_t a = 0;
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        if (s < nrows && (s + 1) * kWave > n_run) {
-          const int need3 = (kv && wait[s] && chk[s] > 0) ? kv_blocks(chk[s], sh) : 0;
-          int cum = bcarry;
-          if (kv) {
-            cum += scan_add32(need3);
-            bcarry = uni(lane_last(cum));
+        dm[s] &= ballot(s * kWave + ln < n_run);
+        if (e.need_A) a += (int64_t)chk[s] * cx[s] + (int64_t)chk[s] * (chk[s] + 1) / 2;
+      }
+      A = e.need_A ? wave_sum64(a) : 0;
+      csum = e.need_C ? dec_context(dm) : 0;
+    }
+    if (!preempted && n_list > n_run && n_run < M && left > 0) {
+      // admissions: a prefix of the waiting requests, cut where the budget, the
+      // sequence cap or the blocks of a first chunk run out
+      const int lim = min(nwin, M);
+      const int left0 = left, room1 = room, P0 = P;
+      const int64_t A0 = A;
+      const int fill0 = fillc;
+      const int64_t cfill0 = cfill;
+      int stop = 0, over = 0;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        if (s < nrows && (s + 1) * kWave > n_run && !stop) {
+          const int i = s * kWave + ln;
+          uint64_t m = ballot(i >= n_run && i < lim);
+          while (m && !stop) {
+            if (adm >= kSerialMax) { over = 1; stop = 1; break; }
+            const int l = __builtin_ctzll(m);
+            m &= m - 1;
+            const int r = lane_read(rp[s], l);
+            const int g = min(min(r, e.H), left);
+            const int nb = kv ? kv_blocks(g, sh) : 0;
+            if (nb > room && kv) { stop = 1; break; }
+            room -= nb;
+            left -= g;
+            P += g;
+            adm += 1;
+            chk[s] = ln == l ? g : chk[s];
+            if (e.need_A) A += (int64_t)g * (g + 1) / 2;
+            if (r == g) {
+              fillc += 1;
+              cfill += g;
+              if (EST && s * kWave + l == lp) lf = 1;
+            }
+            if (left == 0) stop = 1;
           }
-          const bool ok = wait[s] && chk[s] > 0 && (!kv || cum <= room);
-          if (wait[s] && !ok) chk[s] = 0;
-          nadm += ok ? 1 : 0;
-          if constexpr (TAIL) nblk += ok ? need3 : 0;
         }
       }
-      admitted = wave_sum32(nadm);
-      if constexpr (TAIL) room -= kv ? wave_sum32(nblk) : 0;
+      if (over) {
+        int bcarry = 0, nblk = 0, pw = 0;
+        unsigned carry = 0;
+        int64_t a = 0, cf = 0;
+        adm = 0;
+        fillc = fill0;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          if (s < nrows && (s + 1) * kWave > n_run) {
+            const int i = s * kWave + ln;
+            const bool wait = i >= n_run && i < lim;
+            const int want = wait ? min(min(rp[s], e.H), left0) : 0;
+            const unsigned excl =
+                min((unsigned)scan_sat(prev_lane(want), left0) + carry, (unsigned)left0);
+            const int g = min(want, left0 - (int)excl);
+            carry = (unsigned)uni(lane_last((int)min(excl + (unsigned)want, (unsigned)left0)));
+            const int need3 = (kv && g > 0) ? kv_blocks(g, sh) : 0;
+            int cum = bcarry;
+            if (kv) {
+              cum += scan_add32(need3);
+              bcarry = uni(lane_last(cum));
+            }
+            const bool ok = wait && g > 0 && (!kv || cum <= room1);
+            if (wait) chk[s] = ok ? g : 0;
+            adm += popc(ballot(ok));
+            nblk += ok ? need3 : 0;
+            pw += ok ? g : 0;
+            if (e.need_A && ok) a += (int64_t)g * (g + 1) / 2;
+            const uint64_t mf = ballot(ok && g == rp[s]);
+            if ((mf >> ln) & 1) cf += g;
+            fillc += popc(mf);
+            if (EST && s == (lp >> 6)) lf |= (int)((mf >> (lp & (kWave - 1))) & 1);
+          }
+        }
+        const int pws = wave_sum32(pw);
+        P = P0 + pws;
+        left = left0 - pws;
+        room = room1 - (kv ? wave_sum32(nblk) : 0);
+        A = A0 + (e.need_A ? wave_sum64(a) : 0);
+        cfill = cfill0 + (e.need_C ? wave_sum64(cf) : 0);
+      }
     }
     // features and time
-    int P = 0;
-    int64_t C = 0, A = 0;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      if (s < nrows) {
-        P += chk[s];
-        if (e.need_C && dec[s]) C += cx[s];
-        if (e.need_A && chk[s])
-          A += (int64_t)chk[s] * cx[s] + (int64_t)chk[s] * (chk[s] + 1) / 2;
-      }
-    }
-    P = prefill_any ? wave_sum32(P) : 0;
-    if (e.need_C) C = wave_sum64(C);
-    if (e.need_A) A = wave_sum64(A);
+    const int64_t C = csum;
     LStep o;
     o.T = batch_time(e.k, P, D, C, A);
+    o.P = P; o.D = D; o.np = np; o.C = C; o.A = A; o.gg = gg;
     o.tail_ok = false;
-    if constexpr (TAIL)
-      o.tail_ok = !preempted && admitted == n_list - n_run && n_run + admitted < M &&
-                  L1 - P > 0 && (!kv || room >= 1);
-    // the last list entry (an estimate's query)
-    const int lp = n_list - 1;
-    bool ld = false, lf = false;
+    o.same = false;
+    o.last_dec = false;
+    o.last_fill = lf != 0;
+    if constexpr (TAIL) {
+      o.tail_ok = !preempted && adm == n_list - n_run && n_run + adm < M && L1 - P > 0 &&
+                  (!kv || room >= 1);
+      if (o.tail_ok) return o;
+    }
+    if constexpr (EST) {
 #pragma unroll
-    for (int s = 0; s < KS; ++s)
-      if (s == (lp >> 6) && ln == (lp & (kWave - 1))) {
-        ld = dec[s] != 0;
-        lf = chk[s] > 0 && chk[s] == rp[s];
-      }
-    o.last_dec = ballot(ld) != 0;
-    o.last_fill = ballot(lf) != 0;
+      for (int s = 0; s < KS; ++s)
+        if (s == (lp >> 6)) o.last_dec = ((dm[s] >> (lp & (kWave - 1))) & 1) != 0;
+    }
     if constexpr (TRK) {
       const double end = __dadd_rn(clk0, o.T);
       int hit = 0;
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         if (s < nrows) {
-          const bool first =
-              tk->reading == 1 ? (chk[s] > 0 && chk[s] == rp[s]) : dec[s] != 0;
+          const bool first = tk->reading == 1 ? (chk[s] > 0 && chk[s] == rp[s])
+                                              : ((dm[s] >> ln) & 1) != 0;
           const int q = tg[s] - tk->tag0;
           if (first && tg[s] >= 0 && q >= 0 && q < tk->N) {
             tk->out[q] = end;
@@ -515,22 +720,117 @@ struct LQueue {
       ntrk -= wave_sum32(hit);
     }
     // apply; decoding requests whose predicted decode is used up leave
-    bool fin[KS];
+    uint64_t (&fm)[KS] = dm;   // (the decoding ones' masks are spent row by row)
     int nf = 0;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      fin[s] = false;
       if (s < nrows) {
-        if (dec[s]) { cx[s] += 1; rd[s] -= 1; }
-        if (chk[s]) { cx[s] += chk[s]; rp[s] -= chk[s]; }
-        fin[s] = dec[s] && rd[s] == 0;
-        nf += fin[s] ? 1 : 0;
+        const int d = (int)((dm[s] >> ln) & 1);
+        cx[s] += d + chk[s];
+        rd[s] -= d;
+        rp[s] -= chk[s];
+        fm[s] = ballot(d != 0 && rd[s] == 0);
+        nf += popc(fm[s]);
       }
     }
-    n_run += admitted;
-    nf = wave_sum32(nf);
-    if (nf > 0) compact<TRK>(e, tags, fin, nf);
+    n_run += adm;
+    if (kv) held = e.K - room;
+    csum += D + cfill;
+    nfin = preempted || fillc > 0 || nfin <= 1 ? 0 : nfin - 1;
+    if (nf > 0) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        uint64_t m = fm[s];
+        while (m) {
+          const int l = __builtin_ctzll(m);
+          m &= m - 1;
+          const int c = lane_read(cx[s], l);
+          held -= kv ? kv_blocks(c, sh) : 0;
+          csum -= c;
+        }
+      }
+      nfin = 0;
+      compact<TRK, LIVE>(e, tags, fm, nf);
+    } else {
+      o.same = same && !preempted && adm == 0 && fillc == 0 && D + P > 0;
+    }
     return o;
+  }
+
+  // Context of the decoding requests in dm.
+  __device__ int64_t dec_context(const uint64_t (&dm)[KS]) const {
+    const int ln = lane_id();
+    int64_t c = 0;
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      if ((dm[s] >> ln) & 1) c += cx[s];
+    return wave_sum64(c);
+  }
+
+  // Runs the batches after a batch o (with o.same) that serve the same requests the same
+  // tokens: no request is admitted, finishes, completes its prefill or is preempted in
+  // them.  What held back the waiting requests in o still does (no slot or budget comes
+  // free, the free blocks only get fewer).  They differ in C, which grows by D, and A,
+  // which grows by the squared chunks.  Stops before a batch that starts at t_stop or
+  // later; at most `most` batches.  Returns their number; E is the running clock.
+  // Stretches are long where few requests run and a long prompt goes chunk by chunk;
+  // their blocks are bounded from above, so near a full cache the batches are stepped.
+  __device__ __forceinline__ int fold(const LEnv& e, const LStep& o, const int (&chk)[KS],
+                                      double& E, double t_stop, int64_t most) {
+    const int ln = lane_id();
+    const int big = 0x7fffffff;
+    if (nfin == 0) {
+      int x = big;
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+        if (s * kWave + ln < n_run && rp[s] == 0) x = min(x, rd[s]);
+      nfin = wave_min(x);
+    }
+    if (nfin < 3) return 0;
+    int n = nfin == big ? big : nfin - 1;
+    if (o.np > 0) {
+      int x = big;
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+        if (chk[s] > 0) x = min(x, (int)((unsigned)(rp[s] - 1) / (unsigned)chk[s]));
+      n = min(n, wave_min(x));
+    }
+    if ((int64_t)n > most) n = (int)most;
+    if (e.K > 0) {
+      // each decoding request takes at most n / S + 1 blocks, each chunk sum at most one
+      // more than its tokens fill
+      const int64_t grow = (int64_t)o.D * ((n >> e.sh) + 1) + (((int64_t)o.P * n) >> e.sh) +
+                           2 * (int64_t)o.np;
+      if (grow > e.K - held) return 0;
+    }
+    if (n <= 0) return 0;
+    int k = 0;
+    if (!e.need_C && !e.need_A) {
+      for (; k < n && E < t_stop; ++k) E = __dadd_rn(E, o.T);
+    } else {
+      int64_t C = o.C, A = o.A;
+      for (; k < n && E < t_stop; ++k) {
+        C += o.D;
+        A += o.gg;
+        E = __dadd_rn(E, batch_time(e.k, o.P, o.D, C, A));
+      }
+    }
+    n = k;
+    if (n == 0) return 0;
+    int grew = 0;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const bool dec = s * kWave + ln < n_run && rp[s] == 0;
+      const int c0 = cx[s];
+      cx[s] += dec ? n : chk[s] * n;
+      rd[s] -= dec ? n : 0;
+      rp[s] -= dec ? 0 : chk[s] * n;
+      if (dec || chk[s] > 0) grew += kv_blocks(cx[s], e.sh) - kv_blocks(c0, e.sh);
+    }
+    if (e.K > 0) held += wave_sum32(grew);
+    csum += (int64_t)o.D * n;
+    if (nfin != big) nfin -= n;
+    return n;
   }
 };
 

@@ -2,9 +2,11 @@
 // (chunk cap, context limit, KV-cache blocks with recompute preemption; the system
 // appendix lists them among what the simulation follows), on the explicit-list
 // wave engine of sfs_limits.h.  Every estimate simulates its (query, instance) pair
-// batch by batch: from the instance state, or in the clustered trace from the
-// instance's cached admission point (lim_frontier), which gives the same result.
+// batch by batch: from the instance state, or from the instance's admission point
+// (lim_frontier; cached in the clustered trace, shared by the queries of a what-if call),
+// which gives the same result.
 //
+//   k_lfront   one wave per (scenario, instance): admission point for a what-if call.
 //   k_lest     one wave per (scenario, query, instance): what-if estimate.
 //   k_lcommit  one wave per (scenario, instance): append the routed query, replay
 //              to the next arrival.
@@ -26,11 +28,11 @@ namespace lar {
 // the tail, stepped until the query's first decode (reading 1: its prefill
 // completes).  +infinity when the instance's context limit cannot hold the prompt
 // (it cannot take the query); NaN with an error when the state is behind t or the
-// batch cap is reached.
+// batch cap is reached.  it0: batches already folded into q's clock (an admission point).
 template <int KS>
 __device__ __forceinline__ double lim_estimate(const LQueue<KS>& q, const LEnv& e, int p, int d,
                                                double t, int reading, int64_t max_iters,
-                                               int32_t* err, int64_t* it_out) {
+                                               int32_t* err, int64_t it0, int64_t* it_out) {
   const int ln = lane_id();
   *it_out = 0;
   if (q.clock < t) {
@@ -46,61 +48,62 @@ __device__ __forceinline__ double lim_estimate(const LQueue<KS>& q, const LEnv& 
   LQueue<KS> w = q;
   w.template append<false>(e, p, dq, false, nullptr, -1);
   double E = w.clock;
-  int64_t it = 0;
+  int64_t it = it0;
+  int chk[KS];
   for (;;) {
     if (it == max_iters) {
       if (ln == 0) set_error(err, kErrIter);
       *it_out = it;
       return __builtin_nan("");
     }
-    const LStep o = w.template step<false>(e, nullptr, 0.0, nullptr);
+    const LStep o = w.template step<false, false, false>(e, nullptr, 0.0, nullptr, chk);
     E = __dadd_rn(E, o.T);
     ++it;
     if (reading == 1 ? o.last_fill : o.last_dec) break;
+    // (a folded batch neither completes the query's prefill nor follows its completion)
+    if (o.same) it += w.fold(e, o, chk, E, __builtin_inf(), max_iters - it);
   }
   *it_out = it;
   return __dsub_rn(E, t);
 }
 
-// The state of a queue just before the first batch in which a request appended at
-// its tail could be admitted (whatever its prompt).  Batches before that one do not
-// depend on such a request -- it waits behind requests that are not all admitted, or
-// no slot, budget or KV block is left for it, or the batch preempts -- so an estimate
-// from the returned state F, whose clock is the left fold of those batches' times
-// from the queue's own clock, equals the estimate from the queue.  n receives their
-// number.  False (and the error set) when the batch cap is reached first.
+// Brings g to the state just before the first batch in which a request appended at its
+// tail could be admitted (whatever its prompt), its clock folded over the batches before
+// it.  Those batches do not depend on such a request -- it waits behind requests that
+// are not all admitted, or no slot, budget or KV block is left for it, or the batch
+// preempts -- so an estimate from there equals the estimate from where g started.  For
+// the same reason a request that the live queue takes before that point can join the
+// copy, and the search for the next one goes on from it.  n receives the number of
+// batches.  False when `most` batches do not reach it.
 template <int KS>
-__device__ __forceinline__ bool lim_frontier(const LQueue<KS>& q, const LEnv& e, LQueue<KS>& F,
-                                             int64_t& n, int64_t max_iters, int32_t* err) {
-  LQueue<KS> g = q;
+__device__ __forceinline__ bool lim_frontier(LQueue<KS>& g, const LEnv& e, int64_t& n,
+                                             int64_t most) {
   double E = g.clock;
+  int chk[KS];
   n = 0;
   while (g.n_list > 0) {
-    if (n == max_iters) {
-      if (lane_id() == 0) set_error(err, kErrIter);
-      return false;
-    }
-    LQueue<KS> h = g;
-    const LStep o = h.template step<false, true>(e, nullptr, 0.0, nullptr);
-    if (o.tail_ok) break;
+    if (n == most) return false;
+    const LStep o = g.template step<false, false, true>(e, nullptr, 0.0, nullptr, chk);
+    if (o.tail_ok) break;   // (not applied)
     E = __dadd_rn(E, o.T);
     ++n;
-    g = h;
+    if (o.same) n += g.fold(e, o, chk, E, __builtin_inf(), most - n);
   }
-  F = g;
-  F.clock = E;
+  g.clock = E;
   return true;
 }
 
 // Append the query when this queue is the chosen one, then replay every batch that
 // starts before t; an idle queue's clock jumps to t.  TRK: the query is tracked
-// (tag) and first tokens of the replayed batches are recorded.
+// (tag) and first tokens of the replayed batches are recorded.  Returns whether the
+// query was appended.
 template <int KS, bool TRK>
-__device__ __forceinline__ void lim_commit_advance(LQueue<KS>& w, const LEnv& e, bool chosen,
+__device__ __forceinline__ bool lim_commit_advance(LQueue<KS>& w, const LEnv& e, bool chosen,
                                                    int p, int d, double t, int qcap,
                                                    int64_t max_iters, int32_t* err,
                                                    int32_t* tags, int tag, const LTrack& tk) {
   const int ln = lane_id();
+  bool taken = false;
   if (chosen) {
     const int dq = entry_decode(e, p, d);
     if (p < 1 || dq < 1) {
@@ -110,32 +113,61 @@ __device__ __forceinline__ void lim_commit_advance(LQueue<KS>& w, const LEnv& e,
     } else {
       w.template append<TRK>(e, p, dq, true, tags, tag);
       if constexpr (TRK) w.ntrk += 1;
+      taken = true;
     }
   }
   double clock = w.clock;
   int64_t n = 0;
+  int chk[KS];
   while (w.n_list > 0 && clock < t) {
     if (n == max_iters) {
       if (ln == 0) set_error(err, kErrIter);
       break;
     }
-    const LStep o = w.template step<TRK>(e, tags, clock, &tk);
+    const LStep o = w.template step<TRK, true, false>(e, tags, clock, &tk, chk);
     clock = __dadd_rn(clock, o.T);
     ++n;
+    // (folded batches hold no first token: no prefill completes in o or in them)
+    if (o.same) n += w.fold(e, o, chk, clock, t, max_iters - n);
   }
   if (w.n_list == 0 && clock < t) clock = t;
   w.clock = clock;
   w.iters += n;
+  return taken;
+}
+
+// The admission point of every queue, once for all queries of a what-if call: one wave
+// per (scenario, instance).  The batches before it are the same for every query, and
+// under a backlog they are most of an estimate's: 27 instances x 243 queries, full
+// caches, 39 batches an estimate of which 35 come before the admission point.
+template <int KS>
+__global__ __launch_bounds__(kWave) void k_lfront(DevState S, DevParams pr, DevLimits lm, int Z,
+                                                 int I, const double* t_ptr, double t_val,
+                                                 int64_t max_iters, DevFront fr) {
+  const int qid = blockIdx.x;
+  if (qid >= Z * I) return;
+  const double t = t_ptr ? *t_ptr : t_val;
+  __shared__ alignas(16) int lds[lim_lds_words<KS>()];
+  const LEnv e = make_lenv(S, pr, lm, qid, qid % I, lds);
+  LQueue<KS> w;
+  w.template load<false>(S, e, qid, nullptr);
+  int64_t n = 0;
+  // (a state behind t and a batch cap that ends the search are errors only once a query
+  // is estimated: the estimates then start from the state and report them)
+  const int ok = w.clock >= t && lim_frontier(w, e, n, max_iters) ? 1 : 0;
+  w.to_front(fr, qid, ok, n);
 }
 
 // What-if estimates under limits: one wave per (scenario, query, instance), instance
-// fastest; reads the state, changes nothing.
+// fastest, from the queue's admission point when fr has it (fr.win); reads the state,
+// changes nothing.
 template <int KS>
 __global__ __launch_bounds__(kWave) void k_lest(DevState S, DevParams pr, DevLimits lm, int Z,
                                                int Q, int I, const int32_t* q_prefill,
                                                const double* t_ptr, double t_val,
                                                int max_prompt, int reading, int64_t max_iters,
-                                               double* ttft, int32_t* iters, int32_t* err) {
+                                               double* ttft, int32_t* iters, int32_t* err,
+                                               DevFront fr) {
   const int64_t pair = blockIdx.x;
   if (pair >= (int64_t)Z * Q * I) return;
   const int j = (int)(pair % I);
@@ -152,8 +184,14 @@ __global__ __launch_bounds__(kWave) void k_lest(DevState S, DevParams pr, DevLim
     if (lane_id() == 0) set_error(err, kErrArg);
   } else {
     LQueue<KS> w;
-    w.template load<false>(S, e, qid, nullptr);
-    v = lim_estimate(w, e, p, 1, t, reading, max_iters, err, &it);
+    int64_t pre = 0;
+    if (fr.win && uni(fr.sc[qid].ok)) {
+      w.from_front(fr, qid);
+      pre = uni64(fr.sc[qid].pre);
+    } else {
+      w.template load<false>(S, e, qid, nullptr);
+    }
+    v = lim_estimate(w, e, p, 1, t, reading, max_iters, err, pre, &it);
     if (v != v) it = -1;
   }
   if (lane_id() == 0) {
@@ -223,7 +261,8 @@ __global__ __launch_bounds__(NW * kWave) void k_ltrace(LAR_TRACE_PARAMS, DevLimi
       LQueue<KS> w;
       w.template load<false>(S, e, z * I + j, nullptr);
       int64_t it = 0;
-      const double ttft = p_ok ? lim_estimate(w, e, q.p, q.d, q.t, reading, max_iters, err, &it)
+      const double ttft = p_ok ? lim_estimate(w, e, q.p, q.d, q.t, reading, max_iters, err, 0,
+                                               &it)
                                : __builtin_nan("");
       wbatch += it;
       double eq2;
@@ -290,8 +329,9 @@ __global__ __launch_bounds__(W * kWave) void k_ltrace_cl(LAR_TRACE_PARAMS, DevLi
   Cand c;
   c.j = -1; c.u = 0.0; c.ttft = 0.0; c.eq2 = 0.0;
   LQueue<KS> F;             // cached admission point of the owned instance
-  bool f_ok = false;
-  bool f_skip = false;      // the last search found the point at once: estimate directly
+  int f_ok = 0;
+  int f_on = 0;             // F is a state the instance will reach: a search starts there
+  int f_skip = 0;           // the last search found the point at once: estimate directly
   int64_t f_iters = 0;      // the instance's replay count at F
   for (int i = -1; i < N; ++i) {
     const int l = i & (kWave - 1);
@@ -341,12 +381,22 @@ __global__ __launch_bounds__(W * kWave) void k_ltrace_cl(LAR_TRACE_PARAMS, DevLi
         }
       }
       if (own) {
-        lim_commit_advance<KS, TRK>(Q, e, j == m, p, dq, tn, S.qcap, max_iters, err, tags,
-                                    tag0 + i, tk);
-        // F stays the admission point while the replay has not run its batch
-        if (j == m || Q.iters > f_iters || (Q.iters == f_iters && Q.clock != F.clock))
-          f_ok = false;
-        if (j == m) f_skip = false;
+        const bool taken = lim_commit_advance<KS, TRK>(Q, e, j == m, p, dq, tn, S.qcap,
+                                                       max_iters, err, tags, tag0 + i, tk);
+        // F stays the admission point while the replay has not run its batch and the
+        // instance receives no query.  A query it receives waits until F: it joins the
+        // copy there, and the search for the next point goes on from F, so that each
+        // batch is searched once and not again for every query that joins behind it.
+        if (j == m) {
+          if (f_ok && taken) F.join(p, entry_decode(e, p, dq));
+          f_on = f_ok && taken ? 1 : 0;
+          f_ok = 0;
+          f_skip = 0;
+        }
+        if (Q.iters > f_iters || (Q.iters == f_iters && Q.clock != F.clock)) {
+          f_ok = 0;
+          f_on = 0;
+        }
       }
     }
     c.j = -1; c.u = 0.0; c.ttft = 0.0; c.eq2 = 0.0;
@@ -368,16 +418,21 @@ __global__ __launch_bounds__(W * kWave) void k_ltrace_cl(LAR_TRACE_PARAMS, DevLi
           // one, the instance is estimated directly until it receives a query
           if (!f_ok && !f_skip) {
             int64_t nf = 0;
-            f_ok = lim_frontier(Q, e, F, nf, max_iters, err);
-            f_iters = Q.iters + nf;
-            if (f_ok && nf == 0) { f_ok = false; f_skip = true; }
+            if (!f_on) {
+              F = Q;
+              f_iters = Q.iters;
+            }
+            f_ok = lim_frontier(F, e, nf, max_iters - (f_iters - Q.iters)) ? 1 : 0;
+            f_iters += nf;
+            f_on = 0;
+            // (a search that the batch cap ends leaves the error to the estimate)
+            if (f_ok && f_iters == Q.iters) { f_ok = 0; f_skip = 1; }
           }
           if (f_ok) {
-            const int64_t pre = f_iters - Q.iters;   // batches before F, folded in F's clock
-            ttft = lim_estimate(F, e, p1, d1, t1, reading, max_iters - pre, err, &it);
-            it += pre;
+            ttft = lim_estimate(F, e, p1, d1, t1, reading, max_iters, err, f_iters - Q.iters,
+                                &it);
           } else {
-            ttft = lim_estimate(Q, e, p1, d1, t1, reading, max_iters, err, &it);
+            ttft = lim_estimate(Q, e, p1, d1, t1, reading, max_iters, err, 0, &it);
           }
         }
         wbatch += it;
@@ -418,14 +473,16 @@ __global__ __launch_bounds__(kWave) void k_ldrain(DevState S, DevParams pr, DevL
   const LTrack tk{realized + (int64_t)z * N, tag0, N, reading};
   double clock = w.clock;
   int64_t n = 0;
+  int chk[KS];
   while (w.ntrk > 0 && w.n_list > 0) {
     if (n == max_iters) {
       if (lane_id() == 0) set_error(err, kErrIter);
       break;
     }
-    const LStep o = w.template step<true>(e, tags, clock, &tk);
+    const LStep o = w.template step<true, true, false>(e, tags, clock, &tk, chk);
     clock = __dadd_rn(clock, o.T);
     ++n;
+    if (o.same) n += w.fold(e, o, chk, clock, __builtin_inf(), max_iters - n);
   }
 }
 
@@ -445,10 +502,19 @@ hipError_t launch_lim_est(const LaunchEnv& env, int Q, const int32_t* q_prefill,
                                  int32_t* iters) {
   const int64_t total = (int64_t)env.Z * Q * env.I;
   if (total > 0x7fffffff) return hipErrorInvalidValue;
+  // One query alone would wait for a second launch and gain nothing.
+  DevFront fr = Q > 1 ? env.F : DevFront{nullptr, nullptr, 0};
+  if (fr.win) {
+    LIM_SWITCH(KSV, hipLaunchKernelGGL(k_lfront<KSV>, dim3(env.Z * env.I), dim3(kWave), 0,
+                                       env.stream, env.S, env.P, env.L, env.Z, env.I, t_ptr,
+                                       t_val, env.max_iters, fr))
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   LIM_SWITCH(KSV, hipLaunchKernelGGL(k_lest<KSV>, dim3((unsigned)total), dim3(kWave), 0,
                                      env.stream, env.S, env.P, env.L, env.Z, Q, env.I,
                                      q_prefill, t_ptr, t_val, env.max_prompt, env.reading,
-                                     env.max_iters, ttft, iters, env.err))
+                                     env.max_iters, ttft, iters, env.err, fr))
   return hipGetLastError();
 }
 
