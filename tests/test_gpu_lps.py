@@ -87,3 +87,22 @@ def test_lps_outside_the_model():
         assert ok.sum() > 0
         np.testing.assert_array_equal(bits(got[ok]), bits(want[ok]))
         ctx.close()
+
+
+@pytest.mark.parametrize("n_inst,n_q,n_scen", [(1, 1, 1), (257, 3, 2), (3, 4097, 1),
+                                               (5, 6143, 1), (2, 32771, 1), (300, 911, 9)])
+def test_lps_query_chunks(n_inst, n_q, n_scen):
+    """Every length of the queries' chunks: 1, 2 with a remainder, the full 16 with a
+    remainder and over two column blocks; chunks never cross a scenario."""
+    wl = make_workload("c3", n_inst=n_inst, n_q=min(n_q, 64), resident=8)
+    q = np.resize(wl.q_prefill, n_q) + np.arange(n_q, dtype=np.int32) % 37
+    prms = [lps_params(wl, seed=s) for s in range(n_scen)]
+    print(f"lps chunks {n_inst} x {n_q} x {n_scen}", flush=True)
+    ctx = LarContext(n_scen, n_inst, max_seqs_cap=256, queue_cap=16, max_prompt=wl.max_prompt)
+    tt = ctx.estimate_lps(_dev_params(prms), T(q, torch.int32), L.LPS_VARIABILITY)
+    assert ctx.status() == 0
+    got = tt.cpu().numpy()
+    for z in range(n_scen):
+        np.testing.assert_array_equal(bits(got[z]), bits(O.lps_matrix(prms[z], q,
+                                                                      L.LPS_VARIABILITY)))
+    ctx.close()
