@@ -502,8 +502,12 @@ hipError_t launch_lim_est(const LaunchEnv& env, int Q, const int32_t* q_prefill,
                                  int32_t* iters) {
   const int64_t total = (int64_t)env.Z * Q * env.I;
   if (total > 0x7fffffff) return hipErrorInvalidValue;
-  // One query alone would wait for a second launch and gain nothing.
-  DevFront fr = Q > 1 ? env.F : DevFront{nullptr, nullptr, 0};
+  // The shared admission points save the repeated batches, not their latency: up to four
+  // waves per SIMD every pair still runs at once and simulates them beside the others,
+  // and a launch of its own would only come on top: 39 instances x 8 queries 36 us
+  // without, 48 with it; 27 x 243 (6561 pairs, full caches) 504 and 338.
+  constexpr int64_t kSimds = 1024;
+  DevFront fr = total > 4 * kSimds ? env.F : DevFront{nullptr, nullptr, 0};
   if (fr.win) {
     LIM_SWITCH(KSV, hipLaunchKernelGGL(k_lfront<KSV>, dim3(env.Z * env.I), dim3(kWave), 0,
                                        env.stream, env.S, env.P, env.L, env.Z, env.I, t_ptr,

@@ -72,12 +72,19 @@ def test_batches(name, terms):
     reading = int(terms)
     print(f"limits batches {name} terms {terms}", flush=True)
     ctx = context_for(wl, flags=reading, max_iters=MAX_ITERS, queue_cap=1024)
-    # what-if estimates from the shared admission points, and one query alone
+    # what-if estimates from the shared admission points (more than 4096 pairs), from the
+    # state, and one query alone
     t = 0.0
+    many = T(np.resize(wl.q_prefill, 900), torch.int32)
+    tm, im = ctx.estimate(many, t)
     tt, it = ctx.estimate(T(wl.q_prefill, torch.int32), t)
     t1, i1 = ctx.estimate(T(wl.q_prefill[:1], torch.int32), t)
     ctx.sync()
     ref_t, ref_i = O.estimate_matrix(wl, range(wl.n_q), range(wl.n_inst), t, reading=reading)[:2]
+    ref_t, ref_i = np.asarray(ref_t), np.asarray(ref_i)
+    rows = np.arange(900) % wl.n_q
+    np.testing.assert_array_equal(bits(tm.cpu().numpy()[0]), bits(ref_t[rows]))
+    np.testing.assert_array_equal(im.cpu().numpy()[0], ref_i[rows])
     np.testing.assert_array_equal(bits(tt.cpu().numpy()[0]), bits(ref_t))
     np.testing.assert_array_equal(it.cpu().numpy()[0], ref_i)
     np.testing.assert_array_equal(bits(t1.cpu().numpy()[0]), bits(ref_t[:1]))
