@@ -504,8 +504,9 @@ hipError_t launch_lim_est(const LaunchEnv& env, int Q, const int32_t* q_prefill,
   if (total > 0x7fffffff) return hipErrorInvalidValue;
   // The shared admission points save the repeated batches, not their latency: up to four
   // waves per SIMD every pair still runs at once and simulates them beside the others,
-  // and a launch of its own would only come on top: 39 instances x 8 queries 36 us
-  // without, 48 with it; 27 x 243 (6561 pairs, full caches) 504 and 338.
+  // and a launch of its own would only come on top.  64 instances, us without and with:
+  // 32 residents each 2048 pairs 25 / 29, 4096 32 / 34, 8192 49 / 46, 15552 78 / 62; 88
+  // residents 62 / 61, 74 / 63, 118 / 70, 183 / 84.  The line is where no load loses.
   constexpr int64_t kSimds = 1024;
   DevFront fr = total > 4 * kSimds ? env.F : DevFront{nullptr, nullptr, 0};
   if (fr.win) {
