@@ -296,9 +296,18 @@ __global__ __launch_bounds__(NW * kWave) void k_ltrace(LAR_TRACE_PARAMS, DevLimi
 // admission point (lim_frontier), which stays valid while the instance receives no
 // query and its replay has not passed that point.  TRK: the replay reports realised
 // TTFT.
+//
+// Registers are bounded so that 4, 4, 3 and 2 workgroups (KS = 1, 2, 4, 8) share a CU:
+// unbounded the compiler takes 144 and 162 at KS = 1 and 2, a CU holds three, and pools
+// that the device no longer holds at once run with their states in HBM (8 instances, 450
+// scenarios: 64 sequences each 13.0 -> 9.6 ms, 128 each 8.9 -> 5.4).  The bound costs
+// spilled registers, 0-3 % on single pools.
+template <int KS>
+constexpr int lim_trace_per_cu() { return KS <= 2 ? 4 : (KS == 4 ? 3 : 2); }
+
 template <int KS, int W, bool TRK>
-__global__ __launch_bounds__(W * kWave) void k_ltrace_cl(LAR_TRACE_PARAMS, DevLimits lm, int G,
-                                                        uint64_t* xslot, SyncCtl sc) {
+__global__ __launch_bounds__(W * kWave, lim_trace_per_cu<KS>()) void k_ltrace_cl(
+    LAR_TRACE_PARAMS, DevLimits lm, int G, uint64_t* xslot, SyncCtl sc) {
   __shared__ double s_u[2][W];
   __shared__ int s_j[2][W];
   __shared__ int s_abort;
