@@ -21,6 +21,8 @@
 // kept in arrival order, running requests first.  Its first KS*64 entries (KS*64 >= M,
 // so every entry a batch can touch) sit in registers, list position s*64 + lane in
 // slot s; the rest stay in the queue's HBM ring at index (head + position) mod rcap.
+// (Every member function is inlined by force: past some size the compiler calls it
+// instead, and the queue then lives in scratch memory.)
 // A batch's decode tokens and new blocks are counted by ballots; the blocks held and
 // the context of the decoding requests are carried from batch to batch.  The chunks
 // and admissions go to the few requests that get budget, one by one in list order on
@@ -131,6 +133,76 @@ struct LStep {
   int64_t C, A, gg;  // context and attention features, sum of the squared chunks
 };
 
+// A set of window entries.  Up to four rows: the lanes of each row, wave-uniform (SGPRs,
+// counted and scanned by the scalar unit).  More rows: one word per lane, bit s for row
+// s.  Sixteen rows of wave-uniform masks, several sets at once, are more SGPRs than there
+// are: spilled, they doubled the instructions of an estimate.  set() and rest() together
+// give the number of entries.
+template <int KS>
+struct RowSet {
+  static constexpr bool kWide = KS > 4;
+  uint64_t m[kWide ? 1 : KS];
+  uint32_t b;
+
+  __device__ __forceinline__ RowSet() : b(0) {
+#pragma unroll
+    for (int s = 0; s < (kWide ? 1 : KS); ++s) m[s] = 0;
+  }
+  // Puts row s's entry of each lane with p in (once per row); its number, if counted here.
+  __device__ __forceinline__ int set(int s, bool p) {
+    if constexpr (kWide) {
+      b |= p ? 1u << s : 0u;
+      return 0;
+    } else {
+      m[s] = ballot(p);
+      return popc(m[s]);
+    }
+  }
+  // What set() left uncounted.
+  __device__ __forceinline__ int rest() const {
+    if constexpr (kWide) return ballot(b != 0) ? wave_sum32(__builtin_popcount(b)) : 0;
+    else return 0;
+  }
+  // The number of entries.
+  __device__ __forceinline__ int count() const {
+    if constexpr (kWide) {
+      return wave_sum32(__builtin_popcount(b));
+    } else {
+      int n = 0;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) n += popc(m[s]);
+      return n;
+    }
+  }
+  // The lanes of row s (s wave-uniform).
+  __device__ __forceinline__ uint64_t row(int s) const {
+    if constexpr (kWide) {
+      return ballot((b >> s) & 1u);
+    } else {
+      uint64_t x = 0;
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+        if (k == s) x = m[k];
+      return x;
+    }
+  }
+  // Whether this lane's entry of row s is in the set.
+  __device__ __forceinline__ int lane(int s) const {
+    if constexpr (kWide) return (int)((b >> s) & 1u);
+    else return (int)((m[s] >> lane_id()) & 1);
+  }
+  // Only the entries before list position n stay.
+  __device__ __forceinline__ void clip(int n) {
+    const int ln = lane_id();
+    if constexpr (kWide) {
+      const int rows = n > ln ? (n - ln + kWave - 1) >> 6 : 0;
+      b &= (1u << rows) - 1u;
+    } else {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) m[s] &= ballot(s * kWave + ln < n);
+    }
+  }
+};
 
 template <int KS>
 struct LQueue {
@@ -152,7 +224,7 @@ struct LQueue {
   int vq_p, vq_d;
 
   template <bool TRK>
-  __device__ void fetch(const LEnv& e, const int32_t* tags, int s, int pos) {
+  __device__ __forceinline__ void fetch(const LEnv& e, const int32_t* tags, int s, int pos) {
     if (vq && pos == n_list - 1) {
       rp[s] = vq_p; rd[s] = vq_d; cx[s] = 0; sq[s] = next_seq - 1;
       if constexpr (TRK) tg[s] = -1;
@@ -166,7 +238,7 @@ struct LQueue {
 
   // Bring list positions nwin .. min(n_list, KS*64) - 1 into the window.
   template <bool TRK>
-  __device__ void refill(const LEnv& e, const int32_t* tags) {
+  __device__ __forceinline__ void refill(const LEnv& e, const int32_t* tags) {
     const int want = min(n_list, KS * kWave);
     if (nwin >= want) return;
     const int ln = lane_id();
@@ -179,7 +251,7 @@ struct LQueue {
   }
 
   template <bool TRK>
-  __device__ void load(const DevState& S, const LEnv& e, int qid, const int32_t* tags) {
+  __device__ __forceinline__ void load(const DevState& S, const LEnv& e, int qid, const int32_t* tags) {
     const QScal* q = S.sc + qid;
     n_list = uni(q->n_pre); n_run = uni(q->n_part); head = uni(q->head);
     next_seq = uni(q->next_seq);
@@ -195,7 +267,7 @@ struct LQueue {
   }
 
   // held, csum and nfin from the window (every running request is in it).
-  __device__ void recount(const LEnv& e) {
+  __device__ __forceinline__ void recount(const LEnv& e) {
     const int ln = lane_id();
     int h = 0;
     int64_t c = 0;
@@ -212,7 +284,7 @@ struct LQueue {
   }
 
   template <bool TRK>
-  __device__ void store(const DevState& S, const LEnv& e, int qid, int32_t* tags) const {
+  __device__ __forceinline__ void store(const DevState& S, const LEnv& e, int qid, int32_t* tags) const {
     const int ln = lane_id();
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -236,12 +308,12 @@ struct LQueue {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   }
 
-  __device__ int waiting() const { return n_list - n_run; }
+  __device__ __forceinline__ int waiting() const { return n_list - n_run; }
 
   // Append a waiting request at the tail (the caller checked p and the capacity).
   // real == false: an estimate's private copy; nothing is written to HBM.
   template <bool TRK>
-  __device__ void append(const LEnv& e, int p, int d, bool real, int32_t* tags, int tag) {
+  __device__ __forceinline__ void append(const LEnv& e, int p, int d, bool real, int32_t* tags, int tag) {
     const int ln = lane_id();
     const int pos = n_list;
     if (nwin == n_list && pos < KS * kWave) {
@@ -270,7 +342,7 @@ struct LQueue {
   }
 
   // Copy to / from a what-if's admission point (a private copy: no arrival numbers).
-  __device__ void to_front(const DevFront& f, int qid, int ok, int64_t pre) const {
+  __device__ __forceinline__ void to_front(const DevFront& f, int qid, int ok, int64_t pre) const {
     const int ln = lane_id();
     int32_t* w = f.win + (int64_t)qid * 3 * f.cap;
 #pragma unroll
@@ -280,7 +352,7 @@ struct LQueue {
     }
     if (ln == 0) f.sc[qid] = LFront{ok, nwin, n_list, n_run, head, held, csum, pre, clock};
   }
-  __device__ void from_front(const DevFront& f, int qid) {
+  __device__ __forceinline__ void from_front(const DevFront& f, int qid) {
     const int ln = lane_id();
     const LFront* q = f.sc + qid;
     nwin = uni(q->nwin); n_list = uni(q->n_list); n_run = uni(q->n_run); head = uni(q->head);
@@ -302,7 +374,7 @@ struct LQueue {
   // A private copy takes the request that the live queue has just appended: into the
   // window when it is that long; else the ring slot already holds it (a copy ahead of
   // its queue has as many requests fewer as its head is further).
-  __device__ void join(int p, int d) {
+  __device__ __forceinline__ void join(int p, int d) {
     const int ln = lane_id();
     const int pos = n_list;
     if (nwin == n_list && pos < KS * kWave) {
@@ -315,8 +387,8 @@ struct LQueue {
     next_seq += 1;
   }
 
-  // The batch when it must preempt.  dm: the decoding requests, nm: those that need a
-  // new block, per row; free0: free blocks; D: their number.
+  // The batch when it must preempt.  dm: the D decoding requests, nm: those of them that
+  // need a new block; free0: free blocks.
   //
   // Decode tokens go in list order, and the victim is always the last running request,
   // so no request that has its token is a victim of this stage: the victims are the
@@ -327,20 +399,17 @@ struct LQueue {
   // chunks, n_run the new running count, D and P the tokens, cfill the context of the
   // requests whose prefill completes; the victims are waiting again (rp, cx updated).
   // Admissions do not happen in such a batch.  Returns the free blocks.
-  __device__ __forceinline__ int compose_preempt(const LEnv& e, const uint64_t (&dm)[KS],
-                                                 const uint64_t (&nm)[KS], int free0,
+  __device__ __forceinline__ int compose_preempt(const LEnv& e, const RowSet<KS>& dm,
+                                                 const RowSet<KS>& nm, int free0,
                                                  int (&chk)[KS], int& D, int& P, int& fillc,
                                                  int64_t& cfill, int& lf) {
     const int ln = lane_id();
     const int sh = e.sh;
     const int run0 = n_run;
-    int run = n_run, freeb = free0, nn = 0;
+    int run = n_run, freeb = free0, nn = nm.count();
     int hb[KS];   // blocks held
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      nn += popc(nm[s]);
-      hb[s] = kv_blocks(cx[s], sh);
-    }
+    for (int s = 0; s < KS; ++s) hb[s] = kv_blocks(cx[s], sh);
     // the row of the last running request, kept while victims are popped from it
     int v_row = -1, v_hb = 0;
     uint64_t v_dm = 0, v_nm = 0;
@@ -350,7 +419,9 @@ struct LQueue {
         v_row = run >> 6;
 #pragma unroll
         for (int k = 0; k < KS; ++k)
-          if (k == v_row) { v_hb = hb[k]; v_dm = dm[k]; v_nm = nm[k]; }
+          if (k == v_row) v_hb = hb[k];
+        v_dm = dm.row(v_row);
+        v_nm = nm.row(v_row);
       }
       return run & (kWave - 1);
     };
@@ -368,13 +439,12 @@ struct LQueue {
     lf = 0;
 #pragma unroll 1
     for (int s = 0; s * kWave < run && left > 0; ++s) {
-      uint64_t md = 0;
+      uint64_t m = ballot(s * kWave + ln < run) & ~dm.row(s);   // partial prefills of this row
+      if (m == 0) continue;
       int r_rp = 0, r_cx = 0, r_hb = 0;
 #pragma unroll
       for (int k = 0; k < KS; ++k)
-        if (k == s) { md = dm[k]; r_rp = rp[k]; r_cx = cx[k]; r_hb = hb[k]; }
-      uint64_t m = ballot(s * kWave + ln < run) & ~md;   // partial prefills of this row
-      if (m == 0) continue;
+        if (k == s) { r_rp = rp[k]; r_cx = cx[k]; r_hb = hb[k]; }
       const int r_w = min(r_rp, e.H);
       const int r_nb = kv_blocks(r_cx + r_w, sh) - r_hb;
       int r_ch = 0;
@@ -419,10 +489,10 @@ struct LQueue {
     return freeb;
   }
 
-  // Remove the finished window entries keeping the order, and
-  // refill the window from the ring.  fm: the finished ones per row.  LIVE: with the arrival numbers.
+  // Remove the finished window entries fm keeping the order, and refill the window from
+  // the ring.  LIVE: with the arrival numbers.
   template <bool TRK, bool LIVE>
-  __device__ void compact(const LEnv& e, const int32_t* tags, const uint64_t (&fm)[KS], int nf) {
+  __device__ __forceinline__ void compact(const LEnv& e, const int32_t* tags, const RowSet<KS>& fm, int nf) {
     const int ln = lane_id();
     int* Srp = e.lds;
     int* Srd = Srp + KS * kWave;
@@ -433,12 +503,12 @@ struct LQueue {
     int first = KS - 1;
 #pragma unroll
     for (int s = KS - 2; s >= 0; --s)
-      if (fm[s] != 0) first = s;
+      if (fm.row(s) != 0) first = s;
     int base = first * kWave;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       if (s < first) continue;
-      const bool keep = s * kWave + ln < nwin && !((fm[s] >> ln) & 1);
+      const bool keep = s * kWave + ln < nwin && !fm.lane(s);
       const uint64_t m = ballot(keep);
       if (keep) {
         const int dst = base + mbcnt(m);
@@ -492,21 +562,20 @@ struct LQueue {
     const int lp = n_list - 1;
     // decoding requests and those of them that need a new block: the ones whose blocks
     // are full
-    uint64_t dm[KS], nm[KS];
+    RowSet<KS> dm, nm;
     int D = 0, need = 0;
     const int smask = (1 << sh) - 1;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      dm[s] = 0; nm[s] = 0; chk[s] = 0;
+      chk[s] = 0;
       if (s < nrows) {
-        dm[s] = ballot(s * kWave + ln < n_run && rp[s] == 0);
-        D += popc(dm[s]);
-        if (kv) {
-          nm[s] = dm[s] & ballot((cx[s] & smask) == 0);
-          need += popc(nm[s]);
-        }
+        const bool dec = s * kWave + ln < n_run && rp[s] == 0;
+        D += dm.set(s, dec);
+        if (kv) need += nm.set(s, dec && (cx[s] & smask) == 0);
       }
     }
+    D += dm.rest();
+    need += nm.rest();
     const int L1 = B - D;
     int left = L1;
     // chunks of the partial prefills, in list order: min(rp, H, budget left).  When the
@@ -522,7 +591,7 @@ struct LQueue {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
           if (s < nrows) {
-            uint64_t m = ballot(s * kWave + ln < n_run) & ~dm[s];
+            uint64_t m = ballot(s * kWave + ln < n_run) & ~dm.row(s);
             while (m && left > 0) {
               const int l = __builtin_ctzll(m);
               m &= m - 1;
@@ -555,7 +624,7 @@ struct LQueue {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
           if (s < nrows && carry < (unsigned)L1) {
-            const uint64_t pm = ballot(s * kWave + ln < n_run) & ~dm[s];
+            const uint64_t pm = ballot(s * kWave + ln < n_run) & ~dm.row(s);
             if (pm == 0) continue;
             const int want = (pm >> ln) & 1 ? min(min(rp[s], e.H), L1) : 0;
             const unsigned excl =
@@ -595,9 +664,9 @@ struct LQueue {
       room = compose_preempt(e, dm, nm, room0, chk, D, P, fillc, cfill, lf);
       same = 0;
       int64_t a = 0;
+      dm.clip(n_run);
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        dm[s] &= ballot(s * kWave + ln < n_run);
         if (e.need_A) a += (int64_t)chk[s] * cx[s] + (int64_t)chk[s] * (chk[s] + 1) / 2;
       }
       A = e.need_A ? wave_sum64(a) : 0;
@@ -697,9 +766,7 @@ struct LQueue {
       if (o.tail_ok) return o;
     }
     if constexpr (EST) {
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
-        if (s == (lp >> 6)) o.last_dec = ((dm[s] >> (lp & (kWave - 1))) & 1) != 0;
+      o.last_dec = lp < KS * kWave && ((dm.row(lp >> 6) >> (lp & (kWave - 1))) & 1) != 0;
     }
     if constexpr (TRK) {
       const double end = __dadd_rn(clk0, o.T);
@@ -708,7 +775,7 @@ struct LQueue {
       for (int s = 0; s < KS; ++s) {
         if (s < nrows) {
           const bool first = tk->reading == 1 ? (chk[s] > 0 && chk[s] == rp[s])
-                                              : ((dm[s] >> ln) & 1) != 0;
+                                              : dm.lane(s) != 0;
           const int q = tg[s] - tk->tag0;
           if (first && tg[s] >= 0 && q >= 0 && q < tk->N) {
             tk->out[q] = end;
@@ -720,33 +787,45 @@ struct LQueue {
       ntrk -= wave_sum32(hit);
     }
     // apply; decoding requests whose predicted decode is used up leave
-    uint64_t (&fm)[KS] = dm;   // (the decoding ones' masks are spent row by row)
+    RowSet<KS> fm;
     int nf = 0;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       if (s < nrows) {
-        const int d = (int)((dm[s] >> ln) & 1);
+        const int d = dm.lane(s);
         cx[s] += d + chk[s];
         rd[s] -= d;
         rp[s] -= chk[s];
-        fm[s] = ballot(d != 0 && rd[s] == 0);
-        nf += popc(fm[s]);
+        nf += fm.set(s, d != 0 && rd[s] == 0);
       }
     }
+    nf += fm.rest();
     n_run += adm;
     if (kv) held = e.K - room;
     csum += D + cfill;
     nfin = preempted || fillc > 0 || nfin <= 1 ? 0 : nfin - 1;
     if (nf > 0) {
+      if constexpr (RowSet<KS>::kWide) {
+        int h = 0;
+        int64_t c = 0;
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        uint64_t m = fm[s];
-        while (m) {
-          const int l = __builtin_ctzll(m);
-          m &= m - 1;
-          const int c = lane_read(cx[s], l);
-          held -= kv ? kv_blocks(c, sh) : 0;
-          csum -= c;
+        for (int s = 0; s < KS; ++s) {
+          h += fm.lane(s) ? kv_blocks(cx[s], sh) : 0;
+          c += fm.lane(s) ? cx[s] : 0;
+        }
+        held -= kv ? wave_sum32(h) : 0;
+        csum -= e.need_C ? wave_sum64(c) : 0;
+      } else {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          uint64_t m = fm.row(s);
+          while (m) {
+            const int l = __builtin_ctzll(m);
+            m &= m - 1;
+            const int c = lane_read(cx[s], l);
+            held -= kv ? kv_blocks(c, sh) : 0;
+            csum -= c;
+          }
         }
       }
       nfin = 0;
@@ -758,12 +837,11 @@ struct LQueue {
   }
 
   // Context of the decoding requests in dm.
-  __device__ int64_t dec_context(const uint64_t (&dm)[KS]) const {
-    const int ln = lane_id();
+  __device__ __forceinline__ int64_t dec_context(const RowSet<KS>& dm) const {
     int64_t c = 0;
 #pragma unroll
     for (int s = 0; s < KS; ++s)
-      if ((dm[s] >> ln) & 1) c += cx[s];
+      if (dm.lane(s)) c += cx[s];
     return wave_sum64(c);
   }
 

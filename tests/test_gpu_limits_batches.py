@@ -64,13 +64,7 @@ POOLS = {
 }
 
 
-@pytest.mark.parametrize("terms", [False, True])
-@pytest.mark.parametrize("name", sorted(POOLS))
-def test_batches(name, terms):
-    kw = POOLS[name]
-    wl = _pool(900 + len(name), terms=terms, **kw)
-    reading = int(terms)
-    print(f"limits batches {name} terms {terms}", flush=True)
+def _against_oracle(wl, reading):
     ctx = context_for(wl, flags=reading, max_iters=MAX_ITERS, queue_cap=1024)
     # what-if estimates from the shared admission points (more than 4096 pairs), from the
     # state, and one query alone
@@ -105,3 +99,46 @@ def test_batches(name, terms):
     np.testing.assert_array_equal(bits(real.cpu().numpy()[0]), bits(ref.realized))
     assert_state_equal(ctx, 0, ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("terms", [False, True])
+@pytest.mark.parametrize("name", sorted(POOLS))
+def test_batches(name, terms):
+    kw = POOLS[name]
+    wl = _pool(900 + len(name), terms=terms, **kw)
+    print(f"limits batches {name} terms {terms}", flush=True)
+    _against_oracle(wl, int(terms))
+
+
+# windows of 8 and 16 rows with requests running in the upper ones
+DEEP = {
+    "preempt_300": dict(M=300, B=330, res=420, prompt=(1, 12), decode=(2, 40), H=4, S=4, slack=0,
+                        gap=300.0),
+    "admissions_400": dict(M=400, B=900, res=500, prompt=(1, 6), decode=(1, 9), H=0, S=1,
+                           slack=30, gap=300.0),
+    "folds_330": dict(M=330, B=2000, res=330, prompt=(1, 12), decode=(150, 300), H=5, S=8,
+                      slack=9000, gap=2000.0),
+    "preempt_700": dict(M=700, B=760, res=900, prompt=(1, 8), decode=(2, 40), H=2, S=1, slack=1,
+                        gap=600.0),
+    "partials_700": dict(M=700, B=720, res=700, prompt=(1, 9), decode=(1, 6), H=1, S=2, slack=3,
+                         gap=600.0),
+    "no_cache_650": dict(M=650, B=800, res=1000, prompt=(1, 6), decode=(1, 20), H=3, S=1,
+                         slack=None, gap=600.0),
+    "admissions_1000": dict(M=1000, B=1500, res=1100, prompt=(1, 5), decode=(1, 12), H=3, S=2,
+                            slack=200, gap=600.0),
+}
+
+
+@pytest.mark.parametrize("terms", [False, True])
+@pytest.mark.parametrize("name", sorted(DEEP))
+def test_deep_windows(name, terms):
+    kw = DEEP[name]
+    # the first seed whose pool runs requests in the row of M / 2 and, beyond M, lists more
+    for seed in range(100):
+        wl = _pool(seed, terms=terms, **kw)
+        run = max(int((wl.instance_requests(j)[2] > 0).sum()) for j in range(5))
+        if 2 * run > kw["M"] and np.diff(wl.offsets).max() > min(kw["M"], 0.9 * kw["res"]):
+            break
+    assert 2 * run > kw["M"] and run > 128
+    print(f"limits deep windows {name} terms {terms} seed {seed}: {run} running", flush=True)
+    _against_oracle(wl, int(terms))

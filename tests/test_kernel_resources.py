@@ -58,6 +58,18 @@ def kernels():
     return out
 
 
+def test_limits_queues_stay_in_registers(kernels):
+    """A wave of the engine under limits keeps its queue in registers at every width:
+    scratch memory holds spilled registers at most, no arrays."""
+    names = [n for n in kernels if any(f"{len(k)}{k}I" in n for k in (
+        "k_lfront", "k_lest", "k_lcommit", "k_ltrace", "k_ltrace_cl", "k_ldrain"))]
+    assert len(names) >= 40
+    for n in names:
+        k = kernels[n]
+        spilled = 4 * k[".vgpr_spill_count"]
+        assert k[".private_segment_fixed_size"] <= spilled + 16, n
+
+
 @pytest.mark.parametrize("slots,per_cu", [(1, 4), (2, 4), (4, 3), (8, 2)])
 def test_limits_traces_share_a_cu(kernels, slots, per_cu):
     """4-wave workgroups of the clustered trace under limits that one CU holds: a SIMD has
