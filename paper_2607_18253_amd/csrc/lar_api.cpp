@@ -287,7 +287,7 @@ lar_status lar_load_state(lar_ctx* ctx, const lar_instance_params* params, const
     for (int j = 0; j < I; ++j) {
       const lar_sched_limits& L = ctx->lim[j];
       int nr = 0, nw = 0, n = 0;
-      int64_t held = 0, ps = 0;
+      int64_t held = 0, c0 = 0;
       for (int r = offsets[j]; r < offsets[j + 1]; ++r) {
         const int32_t rp = rem_prefill[r], cx = context[r];
         int32_t rd = rem_decode[r];
@@ -308,6 +308,7 @@ lar_status lar_load_state(lar_ctx* ctx, const lar_instance_params* params, const
             return fail(ctx, LAR_E_STATE, "instance %d: more than max_seqs running", j);
           ++nr;
           if (L.kv_blocks > 0) held += (cx + (int64_t)L.block_size - 1) / L.block_size;
+          if (rp == 0) c0 += cx;
         } else {
           if (nw >= qcap)
             return fail(ctx, LAR_E_CAPACITY, "instance %d: more than queue_cap waiting", j);
@@ -315,7 +316,6 @@ lar_status lar_load_state(lar_ctx* ctx, const lar_instance_params* params, const
         }
         const size_t x = (size_t)j * rcap + n;
         r_rp[x] = rp; r_rd[x] = rd; r_cx[x] = cx; r_seq[x] = n;
-        ps += rp;
         ++n;
       }
       if (L.kv_blocks > 0 && held > L.kv_blocks)
@@ -327,7 +327,8 @@ lar_status lar_load_state(lar_ctx* ctx, const lar_instance_params* params, const
       q.n_pre = n;
       q.head = 0;
       q.next_seq = n;
-      q.pre_sum = ps;
+      q.c0sum = c0;        // context of the decoding requests
+      q.pre_sum = held;    // KV blocks of the running ones
       q.clock = clock_ms[j];
       sc[j] = q;
     }

@@ -23,17 +23,17 @@
 // slot s; the rest stay in the queue's HBM ring at index (head + position) mod rcap.
 // (Every member function is inlined by force: past some size the compiler calls it
 // instead, and the queue then lives in scratch memory.)
+//
 // A batch's decode tokens and new blocks are counted by ballots; the blocks held and
-// the context of the decoding requests are carried from batch to batch.  The chunks
-// and admissions go to the few requests that get budget, one by one in list order on
-// the scalar unit (kSerialMax of them; past that by saturating DPP prefix sums and a
-// prefix rule), and a batch that must preempt pops its victims the same way.  Batches
-// that repeat the one before are folded (LQueue::fold).  One wave per SIMD runs at the
-// latency of its dependent instructions, so their number is the engine's time: about
-// 770 a batch where a full KV cache preempts.  Against wave sums for every count, prefix
-// sums over every row and one lane walking lists in LDS to preempt (and without the
-// shared and carried admission points of sfs_limits.hip): 27 instances x 243 queries 504 -> 338 us, 32
-// instances, 6000 queries 158 -> 127 ms.
+// the context of the decoding requests are carried from batch to batch, and in QScal
+// from one kernel to the next.  Chunks and admissions are saturating DPP prefix sums
+// over the rows that hold any; a batch that must preempt pops its victims one by one.
+// Batches that repeat the one before are folded (LQueue::fold).  One wave per SIMD runs at the
+// latency of its dependent instructions, so their number is the engine's time.  Against
+// wave sums for every count and one lane walking lists in LDS to preempt (and without the
+// shared and carried admission points of sfs_limits.hip), of 256 sequences each: 27
+// instances x 243 queries 534 -> 331 us; 32 instances, 2500 queries 132 -> 91 ms; of 1024
+// each, 32 x 100 1.59 -> 1.21 ms.
 #pragma once
 
 #include "sfs_device.h"
@@ -49,11 +49,6 @@ struct DevLimits {
 // LDS words per wave of the limits engine: five rows of KS*64 (compaction staging).
 template <int KS>
 constexpr int lim_lds_words() { return 5 * KS * kWave; }
-
-// Requests that one stage of a batch (the partial prefills, then the admissions) serves
-// one by one: each takes about 30 scalar instructions, about as many as one row of
-// prefix sums, and the requests of one stage usually sit in one or two rows.
-constexpr int kSerialMax = 3;
 
 // Admission point of each queue for the queries of one what-if call: the window
 // (three rows of cap entries per queue) and the scalars.
@@ -127,10 +122,10 @@ struct LStep {
   bool last_dec;   // the last list entry received a decode token
   bool last_fill;  // the last list entry's prefill completed
   bool tail_ok;    // (TAIL steps) a new request at the tail could have been admitted
-  bool same;       // the next batch serves the same requests the same tokens, unless a
-                   // decoding request finishes in it or the KV cache runs short
-  int P, D, np;    // prefill and decode tokens, requests with a chunk
-  int64_t C, A, gg;  // context and attention features, sum of the squared chunks
+  bool same;       // the next batch serves the same requests the same tokens, unless one
+                   // finishes or completes its prefill in it or the KV cache runs short
+  int P, D;        // prefill and decode tokens
+  int64_t C, A;    // context and attention features
 };
 
 // A set of window entries.  Up to four rows: the lanes of each row, wave-uniform (SGPRs,
@@ -213,8 +208,8 @@ struct LQueue {
   int head;      // ring index of list position 0
   int next_seq;
   int ntrk;      // tracked queries without a first token (tracking replays)
-  int held;      // KV blocks of the running requests (K > 0)
-  int64_t csum;  // context of the decoding requests (d != 0)
+  int held;      // KV blocks of the running requests (K > 0; kept in QScal::pre_sum)
+  int64_t csum;  // context of the decoding requests (d != 0; kept in QScal::c0sum)
   int nfin;      // batches to the first finish of a decoding request; 0: not known
   double clock;
   int64_t iters;
@@ -256,6 +251,9 @@ struct LQueue {
     n_list = uni(q->n_pre); n_run = uni(q->n_part); head = uni(q->head);
     next_seq = uni(q->next_seq);
     ntrk = TRK ? uni(q->ntrk) : 0;
+    held = (int)uni64(q->pre_sum);
+    csum = uni64(q->c0sum);
+    nfin = 0;
     clock = q->clock;
     iters = uni64(q->iters);
     vq = false; vq_p = 0; vq_d = 0;
@@ -263,24 +261,6 @@ struct LQueue {
 #pragma unroll
     for (int s = 0; s < KS; ++s) { rp[s] = 0; rd[s] = 0; cx[s] = 0; sq[s] = 0; tg[s] = -1; }
     refill<TRK>(e, tags);
-    recount(e);
-  }
-
-  // held, csum and nfin from the window (every running request is in it).
-  __device__ __forceinline__ void recount(const LEnv& e) {
-    const int ln = lane_id();
-    int h = 0;
-    int64_t c = 0;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      if (s * kWave + ln < n_run) {
-        h += kv_blocks(cx[s], e.sh);
-        if (rp[s] == 0) c += cx[s];
-      }
-    }
-    held = e.K > 0 ? wave_sum32(h) : 0;
-    csum = e.need_C ? wave_sum64(c) : 0;
-    nfin = 0;
   }
 
   template <bool TRK>
@@ -299,7 +279,7 @@ struct LQueue {
     if (ln == 0) {
       QScal* q = S.sc + qid;
       q->g = 0; q->n_dec = 0; q->n_part = n_run; q->n_pre = n_list; q->head = head;
-      q->next_seq = next_seq; q->c0sum = 0; q->pre_sum = 0; q->clock = clock;
+      q->next_seq = next_seq; q->c0sum = csum; q->pre_sum = held; q->clock = clock;
       q->iters = iters;
       if constexpr (TRK) { q->ntrk = ntrk; q->pend = 0; }
     }
@@ -396,13 +376,12 @@ struct LQueue {
   // that needs a block one.  Then the partial prefills in list order, each popping
   // victims until its blocks fit or it is out itself; a victim that holds a decode
   // token of this batch returns it and the block it took.  On return chk holds the
-  // chunks, n_run the new running count, D and P the tokens, cfill the context of the
-  // requests whose prefill completes; the victims are waiting again (rp, cx updated).
+  // chunks, n_run the new running count, D and P the tokens; the victims are waiting again
+  // (rp, cx updated).
   // Admissions do not happen in such a batch.  Returns the free blocks.
   __device__ __forceinline__ int compose_preempt(const LEnv& e, const RowSet<KS>& dm,
                                                  const RowSet<KS>& nm, int free0,
-                                                 int (&chk)[KS], int& D, int& P, int& fillc,
-                                                 int64_t& cfill, int& lf) {
+                                                 int (&chk)[KS], int& D, int& P) {
     const int ln = lane_id();
     const int sh = e.sh;
     const int run0 = n_run;
@@ -434,9 +413,6 @@ struct LQueue {
     freeb -= nn;
     int left = e.k.B - D;
     P = 0;
-    fillc = 0;
-    cfill = 0;
-    lf = 0;
 #pragma unroll 1
     for (int s = 0; s * kWave < run && left > 0; ++s) {
       uint64_t m = ballot(s * kWave + ln < run) & ~dm.row(s);   // partial prefills of this row
@@ -472,10 +448,6 @@ struct LQueue {
         P += g;
         if (left == 0) break;
       }
-      const uint64_t mf = ballot(r_ch > 0 && r_ch == r_rp);
-      fillc += popc(mf);
-      if (e.need_C) cfill += sum_lanes64(r_cx + r_ch, mf);
-      if ((n_list - 1) >> 6 == s) lf = (int)((mf >> ((n_list - 1) & (kWave - 1))) & 1);
 #pragma unroll
       for (int k = 0; k < KS; ++k)
         if (k == s) chk[k] = r_ch;
@@ -582,77 +554,32 @@ struct LQueue {
     // decode tokens alone run out of blocks the preempting pass gives them.
     const int room0 = kv ? e.K - held : 0;   // free blocks
     int preempted = kv && need > room0 ? 1 : 0;
-    int P = 0, np = 0, fillc = 0;
-    int64_t A = 0, gg = 0, cfill = 0;
-    int same = 1, lf = 0;   // (ints: a bool across blocks would be a lane mask)
+    int P = 0;
+    int64_t A = 0;
     if (n_run > D && left > 0 && !preempted) {
-      int needp = 0;
-      if (n_run - D <= kSerialMax) {
+      // exclusive saturating prefix sums, row by row where there are any
+      unsigned carry = 0;
+      int nd = 0;
+      int64_t a = 0;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-          if (s < nrows) {
-            uint64_t m = ballot(s * kWave + ln < n_run) & ~dm.row(s);
-            while (m && left > 0) {
-              const int l = __builtin_ctzll(m);
-              m &= m - 1;
-              const int r = lane_read(rp[s], l);
-              const int c = lane_read(cx[s], l);
-              const int g = min(min(r, e.H), left);
-              left -= g;
-              P += g;
-              np += 1;
-              chk[s] = ln == l ? g : chk[s];
-              needp += kv_blocks(c + g, sh) - kv_blocks(c, sh);
-              if (e.need_A) {
-                A += (int64_t)g * c + (int64_t)g * (g + 1) / 2;
-                gg += (int64_t)g * g;
-              }
-              if (r - g <= g) same = 0;
-              if (r == g) {
-                fillc += 1;
-                cfill += c + g;
-                if (EST && s * kWave + l == lp) lf = 1;
-              }
-            }
-          }
-        }
-      } else {
-        // exclusive saturating prefix sums, row by row where there are any
-        unsigned carry = 0;
-        int nd = 0;
-        int64_t a = 0, g2 = 0;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-          if (s < nrows && carry < (unsigned)L1) {
-            const uint64_t pm = ballot(s * kWave + ln < n_run) & ~dm.row(s);
-            if (pm == 0) continue;
-            const int want = (pm >> ln) & 1 ? min(min(rp[s], e.H), L1) : 0;
-            const unsigned excl =
-                min((unsigned)scan_sat(prev_lane(want), L1) + carry, (unsigned)L1);
-            const int g = min(want, L1 - (int)excl);
-            chk[s] = g;
-            carry = (unsigned)uni(lane_last((int)min(excl + (unsigned)want, (unsigned)L1)));
-            if (kv) nd += kv_blocks(cx[s] + g, sh) - kv_blocks(cx[s], sh);
-            if (e.need_A) {
-              a += (int64_t)g * cx[s] + (int64_t)g * (g + 1) / 2;
-              g2 += (int64_t)g * g;
-            }
-            const uint64_t mf = ballot(g > 0 && g == rp[s]);
-            fillc += popc(mf);
-            np += popc(ballot(g > 0));
-            if (ballot(g > 0 && rp[s] - g <= g)) same = 0;
-            if (e.need_C) cfill += sum_lanes64(cx[s] + g, mf);
-            if (EST && s == (lp >> 6)) lf |= (int)((mf >> (lp & (kWave - 1))) & 1);
-          }
-        }
-        P = (int)carry;
-        left = L1 - P;
-        if (kv) needp = wave_sum32(nd);
-        if (e.need_A) {
-          A = wave_sum64(a);
-          gg = wave_sum64(g2);
+      for (int s = 0; s < KS; ++s) {
+        if (s < nrows && carry < (unsigned)L1) {
+          const uint64_t pm = ballot(s * kWave + ln < n_run) & ~dm.row(s);
+          if (pm == 0) continue;
+          const int want = (pm >> ln) & 1 ? min(min(rp[s], e.H), L1) : 0;
+          const unsigned excl =
+              min((unsigned)scan_sat(prev_lane(want), L1) + carry, (unsigned)L1);
+          const int g = min(want, L1 - (int)excl);
+          chk[s] = g;
+          carry = (unsigned)uni(lane_last((int)min(excl + (unsigned)want, (unsigned)L1)));
+          if (kv) nd += kv_blocks(cx[s] + g, sh) - kv_blocks(cx[s], sh);
+          if (e.need_A) a += (int64_t)g * cx[s] + (int64_t)g * (g + 1) / 2;
         }
       }
+      P = (int)carry;
+      left = L1 - P;
+      const int needp = kv ? wave_sum32(nd) : 0;
+      if (e.need_A) A = wave_sum64(a);
       if (kv && need + needp > room0) preempted = 1;
       need += needp;
     }
@@ -661,8 +588,7 @@ struct LQueue {
     if (preempted) {
 #pragma unroll
       for (int s = 0; s < KS; ++s) chk[s] = 0;
-      room = compose_preempt(e, dm, nm, room0, chk, D, P, fillc, cfill, lf);
-      same = 0;
+      room = compose_preempt(e, dm, nm, room0, chk, D, P);
       int64_t a = 0;
       dm.clip(n_run);
 #pragma unroll
@@ -676,97 +602,62 @@ struct LQueue {
       // admissions: a prefix of the waiting requests, cut where the budget, the
       // sequence cap or the blocks of a first chunk run out
       const int lim = min(nwin, M);
-      const int left0 = left, room1 = room, P0 = P;
-      const int64_t A0 = A;
-      const int fill0 = fillc;
-      const int64_t cfill0 = cfill;
-      int stop = 0, over = 0;
+      const int left0 = left;
+      int bcarry = 0, nblk = 0, pw = 0;
+      unsigned carry = 0;
+      int64_t a = 0;
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        if (s < nrows && (s + 1) * kWave > n_run && !stop) {
+        if (s < nrows && (s + 1) * kWave > n_run) {
           const int i = s * kWave + ln;
-          uint64_t m = ballot(i >= n_run && i < lim);
-          while (m && !stop) {
-            if (adm >= kSerialMax) { over = 1; stop = 1; break; }
-            const int l = __builtin_ctzll(m);
-            m &= m - 1;
-            const int r = lane_read(rp[s], l);
-            const int g = min(min(r, e.H), left);
-            const int nb = kv ? kv_blocks(g, sh) : 0;
-            if (nb > room && kv) { stop = 1; break; }
-            room -= nb;
-            left -= g;
-            P += g;
-            adm += 1;
-            chk[s] = ln == l ? g : chk[s];
-            if (e.need_A) A += (int64_t)g * (g + 1) / 2;
-            if (r == g) {
-              fillc += 1;
-              cfill += g;
-              if (EST && s * kWave + l == lp) lf = 1;
-            }
-            if (left == 0) stop = 1;
+          const bool wait = i >= n_run && i < lim;
+          const int want = wait ? min(min(rp[s], e.H), left0) : 0;
+          const unsigned excl =
+              min((unsigned)scan_sat(prev_lane(want), left0) + carry, (unsigned)left0);
+          const int g = min(want, left0 - (int)excl);
+          carry = (unsigned)uni(lane_last((int)min(excl + (unsigned)want, (unsigned)left0)));
+          const int need3 = (kv && g > 0) ? kv_blocks(g, sh) : 0;
+          int cum = bcarry;
+          if (kv) {
+            cum += scan_add32(need3);
+            bcarry = uni(lane_last(cum));
           }
+          const bool ok = wait && g > 0 && (!kv || cum <= room);
+          if (wait) chk[s] = ok ? g : 0;
+          adm += popc(ballot(ok));
+          nblk += ok ? need3 : 0;
+          pw += ok ? g : 0;
+          if (e.need_A && ok) a += (int64_t)g * (g + 1) / 2;
         }
       }
-      if (over) {
-        int bcarry = 0, nblk = 0, pw = 0;
-        unsigned carry = 0;
-        int64_t a = 0, cf = 0;
-        adm = 0;
-        fillc = fill0;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-          if (s < nrows && (s + 1) * kWave > n_run) {
-            const int i = s * kWave + ln;
-            const bool wait = i >= n_run && i < lim;
-            const int want = wait ? min(min(rp[s], e.H), left0) : 0;
-            const unsigned excl =
-                min((unsigned)scan_sat(prev_lane(want), left0) + carry, (unsigned)left0);
-            const int g = min(want, left0 - (int)excl);
-            carry = (unsigned)uni(lane_last((int)min(excl + (unsigned)want, (unsigned)left0)));
-            const int need3 = (kv && g > 0) ? kv_blocks(g, sh) : 0;
-            int cum = bcarry;
-            if (kv) {
-              cum += scan_add32(need3);
-              bcarry = uni(lane_last(cum));
-            }
-            const bool ok = wait && g > 0 && (!kv || cum <= room1);
-            if (wait) chk[s] = ok ? g : 0;
-            adm += popc(ballot(ok));
-            nblk += ok ? need3 : 0;
-            pw += ok ? g : 0;
-            if (e.need_A && ok) a += (int64_t)g * (g + 1) / 2;
-            const uint64_t mf = ballot(ok && g == rp[s]);
-            if ((mf >> ln) & 1) cf += g;
-            fillc += popc(mf);
-            if (EST && s == (lp >> 6)) lf |= (int)((mf >> (lp & (kWave - 1))) & 1);
-          }
-        }
-        const int pws = wave_sum32(pw);
-        P = P0 + pws;
-        left = left0 - pws;
-        room = room1 - (kv ? wave_sum32(nblk) : 0);
-        A = A0 + (e.need_A ? wave_sum64(a) : 0);
-        cfill = cfill0 + (e.need_C ? wave_sum64(cf) : 0);
-      }
+      const int pws = wave_sum32(pw);
+      P += pws;
+      left -= pws;
+      if (kv) room -= wave_sum32(nblk);
+      if (e.need_A) A += wave_sum64(a);
     }
     // features and time
     const int64_t C = csum;
     LStep o;
     o.T = batch_time(e.k, P, D, C, A);
-    o.P = P; o.D = D; o.np = np; o.C = C; o.A = A; o.gg = gg;
+    o.P = P; o.D = D; o.C = C; o.A = A;
     o.tail_ok = false;
     o.same = false;
     o.last_dec = false;
-    o.last_fill = lf != 0;
+    o.last_fill = false;
     if constexpr (TAIL) {
-      o.tail_ok = !preempted && adm == n_list - n_run && n_run + adm < M && L1 - P > 0 &&
+      o.tail_ok = !preempted && adm == n_list - n_run && n_run + adm < M && left > 0 &&
                   (!kv || room >= 1);
       if (o.tail_ok) return o;
     }
     if constexpr (EST) {
-      o.last_dec = lp < KS * kWave && ((dm.row(lp >> 6) >> (lp & (kWave - 1))) & 1) != 0;
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+        if (s == (lp >> 6)) {
+          const uint64_t fill = ballot(chk[s] > 0 && chk[s] == rp[s]);
+          o.last_dec = ((dm.row(s) >> (lp & (kWave - 1))) & 1) != 0;
+          o.last_fill = ((fill >> (lp & (kWave - 1))) & 1) != 0;
+        }
     }
     if constexpr (TRK) {
       const double end = __dadd_rn(clk0, o.T);
@@ -800,6 +691,18 @@ struct LQueue {
       }
     }
     nf += fm.rest();
+    int fillc = 0;       // requests whose prefill this batch completes: they decode next
+    int64_t cfill = 0;   // their context
+    if (P > 0) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        if (s < nrows) {
+          const uint64_t mf = ballot(chk[s] > 0 && rp[s] == 0);
+          fillc += popc(mf);
+          if (e.need_C) cfill += sum_lanes64(cx[s], mf);
+        }
+      }
+    }
     n_run += adm;
     if (kv) held = e.K - room;
     csum += D + cfill;
@@ -831,7 +734,7 @@ struct LQueue {
       nfin = 0;
       compact<TRK, LIVE>(e, tags, fm, nf);
     } else {
-      o.same = same && !preempted && adm == 0 && fillc == 0 && D + P > 0;
+      o.same = !preempted && adm == 0 && fillc == 0 && D + P > 0;
     }
     return o;
   }
@@ -857,6 +760,19 @@ struct LQueue {
                                       double& E, double t_stop, int64_t most) {
     const int ln = lane_id();
     const int big = 0x7fffffff;
+    const int64_t room = e.K - held;
+    // (the blocks of one more batch, bounded as below: near a full cache nothing folds)
+    if (e.K > 0 && (int64_t)o.D * (e.sh == 0 ? 2 : 1) + (o.P >> e.sh) > room) return 0;
+    int np = 0;   // requests with a chunk
+    if (o.P > 0) {
+      uint64_t end = 0;   // those that complete their prefill in the next batch
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        np += popc(ballot(chk[s] > 0));
+        end |= ballot(rp[s] <= chk[s] && chk[s] > 0);
+      }
+      if (end) return 0;
+    }
     if (nfin == 0) {
       int x = big;
 #pragma unroll
@@ -866,7 +782,7 @@ struct LQueue {
     }
     if (nfin < 3) return 0;
     int n = nfin == big ? big : nfin - 1;
-    if (o.np > 0) {
+    if (np > 0) {
       int x = big;
 #pragma unroll
       for (int s = 0; s < KS; ++s)
@@ -878,18 +794,24 @@ struct LQueue {
       // each decoding request takes at most n / S + 1 blocks, each chunk sum at most one
       // more than its tokens fill
       const int64_t grow = (int64_t)o.D * ((n >> e.sh) + 1) + (((int64_t)o.P * n) >> e.sh) +
-                           2 * (int64_t)o.np;
-      if (grow > e.K - held) return 0;
+                           2 * (int64_t)np;
+      if (grow > room) return 0;
     }
     if (n <= 0) return 0;
     int k = 0;
     if (!e.need_C && !e.need_A) {
       for (; k < n && E < t_stop; ++k) E = __dadd_rn(E, o.T);
     } else {
-      int64_t C = o.C, A = o.A;
+      int64_t C = o.C, A = o.A, gg = 0;   // gg: sum of the squared chunks
+      if (e.need_A && np > 0) {
+        int64_t x = 0;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) x += (int64_t)chk[s] * chk[s];
+        gg = wave_sum64(x);
+      }
       for (; k < n && E < t_stop; ++k) {
         C += o.D;
-        A += o.gg;
+        A += gg;
         E = __dadd_rn(E, batch_time(e.k, o.P, o.D, C, A));
       }
     }

@@ -298,10 +298,10 @@ __global__ __launch_bounds__(NW * kWave) void k_ltrace(LAR_TRACE_PARAMS, DevLimi
 // TTFT.
 //
 // Registers are bounded so that 4, 4, 3 and 2 workgroups (KS = 1, 2, 4, 8) share a CU:
-// unbounded the compiler takes 144 and 162 at KS = 1 and 2, a CU holds three, and pools
-// that the device no longer holds at once run with their states in HBM (8 instances, 450
-// scenarios: 64 sequences each 13.0 -> 9.6 ms, 128 each 8.9 -> 5.4).  The bound costs
-// spilled registers, 0-3 % on single pools.
+// unbounded the compiler takes 144, 160, 194 and 236, and pools that the device no longer
+// holds at once run with their states in HBM (8 instances, 450 scenarios, 128 sequences
+// each: 4.9 against 8.2 ms; 300 scenarios, 256 each: 4.6 against 11.3).  The bound costs
+// up to 80 spilled registers, 0-3 % on single pools.
 template <int KS>
 constexpr int lim_trace_per_cu() { return KS <= 2 ? 4 : (KS == 4 ? 3 : 2); }
 
@@ -437,12 +437,11 @@ __global__ __launch_bounds__(W * kWave, lim_trace_per_cu<KS>()) void k_ltrace_cl
             // (a search that the batch cap ends leaves the error to the estimate)
             if (f_ok && f_iters == Q.iters) { f_ok = 0; f_skip = 1; }
           }
-          if (f_ok) {
-            ttft = lim_estimate(F, e, p1, d1, t1, reading, max_iters, err, f_iters - Q.iters,
-                                &it);
-          } else {
-            ttft = lim_estimate(Q, e, p1, d1, t1, reading, max_iters, err, 0, &it);
-          }
+          LQueue<KS> w;
+          if (f_ok) w = F;
+          else w = Q;
+          ttft = lim_estimate(w, e, p1, d1, t1, reading, max_iters, err,
+                              f_ok ? f_iters - Q.iters : 0, &it);
         }
         wbatch += it;
         const double a = read_lane_f64(in_nxt ? nxt.acc[0] : cur.acc[0], l1);
