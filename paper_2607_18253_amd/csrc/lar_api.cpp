@@ -42,7 +42,6 @@ struct lar_ctx {
   bool limited = false;
   std::vector<lar_sched_limits> lim;
   int32_t* plim = nullptr;
-  lar::DevFront front{};       // admission points of a what-if call (lar_set_scheduler)
   int32_t* err = nullptr;
   size_t tail_elems = 0;  // allocated K * Z * I
   bool loaded = false;
@@ -116,7 +115,6 @@ LaunchEnv env_of(const lar_ctx* ctx) {
   e.sync = ctx->sync;
   e.work = ctx->work;
   e.limited = ctx->limited;
-  e.F = ctx->front;
   e.L.H = ctx->plim;
   e.L.K = ctx->plim + ctx->I;
   e.L.sh = ctx->plim + 2 * ctx->I;
@@ -466,17 +464,6 @@ lar_status lar_set_scheduler(lar_ctx* ctx, const lar_sched_limits* limits) {
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   HIP_TRY(ctx, hipMemcpy(ctx->plim, dev.data(), dev.size() * sizeof(int32_t),
                          hipMemcpyHostToDevice));
-  // the admission points of what-if calls; without the memory for them every estimate
-  // starts from the state
-  if (limits && !ctx->front.win) {
-    const size_t ZI = (size_t)ctx->Z * I, cap = (size_t)ctx->ks * 64;
-    int32_t* win = nullptr;
-    lar::LFront* sc = nullptr;
-    if (dev_alloc(ctx, &win, ZI * 3 * cap) == LAR_OK && dev_alloc(ctx, &sc, ZI) == LAR_OK)
-      ctx->front = lar::DevFront{win, sc, (int)cap};
-    else
-      (void)hipGetLastError();
-  }
   ctx->limited = limits != nullptr;
   ctx->lim.assign(limits ? limits : nullptr, limits ? limits + I : nullptr);
   ctx->loaded = false;   // the state layout depends on the scheduler: load again

@@ -40,7 +40,6 @@ struct LaunchEnv {
   // engine of sfs_limits.h on the state laid out for it
   bool limited;
   DevLimits L;
-  DevFront F;         // what-if workspace under limits
 };
 
 constexpr int kMaxCluster = 64;

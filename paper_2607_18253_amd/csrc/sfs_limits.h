@@ -50,20 +50,6 @@ struct DevLimits {
 template <int KS>
 constexpr int lim_lds_words() { return 5 * KS * kWave; }
 
-// Admission point of each queue for the queries of one what-if call: the window
-// (three rows of cap entries per queue) and the scalars.
-struct LFront {
-  int ok;      // 0: no admission point (the estimates start from the state)
-  int nwin, n_list, n_run, head, held;
-  int64_t csum, pre;   // pre: batches folded into clock
-  double clock;
-};
-struct DevFront {
-  int32_t* win;    // [ZI][3][cap]; nullptr: no workspace
-  LFront* sc;      // [ZI]
-  int cap;
-};
-
 struct LEnv {
   Coef k;
   int H;      // chunk cap, INT_MAX when none
@@ -246,7 +232,8 @@ struct LQueue {
   }
 
   template <bool TRK>
-  __device__ __forceinline__ void load(const DevState& S, const LEnv& e, int qid, const int32_t* tags) {
+  __device__ __forceinline__ void load(const DevState& S, const LEnv& e, int qid,
+                                       const int32_t* tags) {
     const QScal* q = S.sc + qid;
     n_list = uni(q->n_pre); n_run = uni(q->n_part); head = uni(q->head);
     next_seq = uni(q->next_seq);
@@ -321,34 +308,46 @@ struct LQueue {
     next_seq += 1;
   }
 
-  // Copy to / from a what-if's admission point (a private copy: no arrival numbers).
-  __device__ __forceinline__ void to_front(const DevFront& f, int qid, int ok, int64_t pre) const {
+  // Copy to / from a what-if's admission point (a private copy: no arrival numbers).  It
+  // is kept where the default engine keeps what this one has no use for: the first mcap
+  // entries in the queue's decode slots, the scalars in its trajectory.  Entries from
+  // position mcap on have never run (at most M <= mcap do, and positions only fall), so
+  // the ring still holds them as they are.  pre: batches folded into the clock.
+  __device__ __forceinline__ void to_front(const DevState& S, const DevTraj& f, int qid,
+                                           int64_t pre) const {
     const int ln = lane_id();
-    int32_t* w = f.win + (int64_t)qid * 3 * f.cap;
+    const int64_t o = (int64_t)qid * S.mcap;
+    const int n = min(nwin, S.mcap);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int x = s * kWave + ln;
-      if (x < nwin) { w[x] = rp[s]; w[f.cap + x] = rd[s]; w[2 * f.cap + x] = cx[s]; }
+      if (x < n) { S.d_last[o + x] = rp[s]; S.d_cx0[o + x] = rd[s]; S.d_seq[o + x] = cx[s]; }
     }
-    if (ln == 0) f.sc[qid] = LFront{ok, nwin, n_list, n_run, head, held, csum, pre, clock};
+    if (ln == 0) {
+      f.P[qid] = n_list; f.left[qid] = n_run; f.pre[qid] = head;
+      f.D[qid] = held; f.C[qid] = csum; f.A[qid] = pre; f.E[qid] = clock;
+    }
   }
-  __device__ __forceinline__ void from_front(const DevFront& f, int qid) {
+  __device__ __forceinline__ void from_front(const DevState& S, const LEnv& e, const DevTraj& f,
+                                             int qid, int64_t* pre) {
     const int ln = lane_id();
-    const LFront* q = f.sc + qid;
-    nwin = uni(q->nwin); n_list = uni(q->n_list); n_run = uni(q->n_run); head = uni(q->head);
-    held = uni(q->held); csum = uni64(q->csum); clock = q->clock;
+    const int64_t o = (int64_t)qid * S.mcap;
+    n_list = (int)uni64(f.P[qid]); n_run = uni(f.left[qid]); head = uni(f.pre[qid]);
+    held = (int)uni64(f.D[qid]); csum = uni64(f.C[qid]); clock = f.E[qid];
+    *pre = uni64(f.A[qid]);
     nfin = 0; next_seq = 0; ntrk = 0; iters = 0;
     vq = false; vq_p = 0; vq_d = 0;
-    const int32_t* w = f.win + (int64_t)qid * 3 * f.cap;
+    nwin = min(n_list, S.mcap);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int x = s * kWave + ln;
       const bool v = x < nwin;
-      rp[s] = v ? w[x] : 0;
-      rd[s] = v ? w[f.cap + x] : 0;
-      cx[s] = v ? w[2 * f.cap + x] : 0;
+      rp[s] = v ? S.d_last[o + x] : 0;
+      rd[s] = v ? S.d_cx0[o + x] : 0;
+      cx[s] = v ? S.d_seq[o + x] : 0;
       sq[s] = 0; tg[s] = -1;
     }
+    refill<false>(e, nullptr);
   }
 
   // A private copy takes the request that the live queue has just appended: into the

@@ -143,7 +143,7 @@ __device__ __forceinline__ bool lim_commit_advance(LQueue<KS>& w, const LEnv& e,
 template <int KS>
 __global__ __launch_bounds__(kWave) void k_lfront(DevState S, DevParams pr, DevLimits lm, int Z,
                                                  int I, const double* t_ptr, double t_val,
-                                                 int64_t max_iters, DevFront fr) {
+                                                 int64_t max_iters, DevTraj fr) {
   const int qid = blockIdx.x;
   if (qid >= Z * I) return;
   const double t = t_ptr ? *t_ptr : t_val;
@@ -154,20 +154,23 @@ __global__ __launch_bounds__(kWave) void k_lfront(DevState S, DevParams pr, DevL
   int64_t n = 0;
   // (a state behind t and a batch cap that ends the search are errors only once a query
   // is estimated: the estimates then start from the state and report them)
-  const int ok = w.clock >= t && lim_frontier(w, e, n, max_iters) ? 1 : 0;
-  w.to_front(fr, qid, ok, n);
+  if (w.clock < t || !lim_frontier(w, e, n, max_iters)) {
+    w.template load<false>(S, e, qid, nullptr);
+    n = 0;
+  }
+  w.to_front(S, fr, qid, n);
 }
 
 // What-if estimates under limits: one wave per (scenario, query, instance), instance
-// fastest, from the queue's admission point when fr has it (fr.win); reads the state,
-// changes nothing.
-template <int KS>
+// fastest; reads the state, changes nothing.  FRONT: from the admission points of
+// k_lfront, else from the state.
+template <int KS, bool FRONT>
 __global__ __launch_bounds__(kWave) void k_lest(DevState S, DevParams pr, DevLimits lm, int Z,
                                                int Q, int I, const int32_t* q_prefill,
                                                const double* t_ptr, double t_val,
                                                int max_prompt, int reading, int64_t max_iters,
                                                double* ttft, int32_t* iters, int32_t* err,
-                                               DevFront fr) {
+                                               DevTraj fr) {
   const int64_t pair = blockIdx.x;
   if (pair >= (int64_t)Z * Q * I) return;
   const int j = (int)(pair % I);
@@ -185,12 +188,8 @@ __global__ __launch_bounds__(kWave) void k_lest(DevState S, DevParams pr, DevLim
   } else {
     LQueue<KS> w;
     int64_t pre = 0;
-    if (fr.win && uni(fr.sc[qid].ok)) {
-      w.from_front(fr, qid);
-      pre = uni64(fr.sc[qid].pre);
-    } else {
-      w.template load<false>(S, e, qid, nullptr);
-    }
+    if constexpr (FRONT) w.from_front(S, e, fr, qid, &pre);
+    else w.template load<false>(S, e, qid, nullptr);
     v = lim_estimate(w, e, p, 1, t, reading, max_iters, err, pre, &it);
     if (v != v) it = -1;
   }
@@ -505,6 +504,18 @@ __global__ __launch_bounds__(kWave) void k_ldrain(DevState S, DevParams pr, DevL
     default: return hipErrorInvalidValue;       \
   }
 
+template <bool FRONT>
+static hipError_t launch_lim_est_from(const LaunchEnv& env, int Q, const int32_t* q_prefill,
+                                      const double* t_ptr, double t_val, double* ttft,
+                                      int32_t* iters) {
+  const int64_t total = (int64_t)env.Z * Q * env.I;
+  LIM_SWITCH(KSV, hipLaunchKernelGGL((k_lest<KSV, FRONT>), dim3((unsigned)total), dim3(kWave),
+                                     0, env.stream, env.S, env.P, env.L, env.Z, Q, env.I,
+                                     q_prefill, t_ptr, t_val, env.max_prompt, env.reading,
+                                     env.max_iters, ttft, iters, env.err, env.T))
+  return hipGetLastError();
+}
+
 hipError_t launch_lim_est(const LaunchEnv& env, int Q, const int32_t* q_prefill,
                                  const double* t_ptr, double t_val, double* ttft,
                                  int32_t* iters) {
@@ -516,19 +527,14 @@ hipError_t launch_lim_est(const LaunchEnv& env, int Q, const int32_t* q_prefill,
   // 32 residents each 2048 pairs 25 / 29, 4096 32 / 34, 8192 49 / 46, 15552 78 / 62; 88
   // residents 62 / 61, 74 / 63, 118 / 70, 183 / 84.  The line is where no load loses.
   constexpr int64_t kSimds = 1024;
-  DevFront fr = total > 4 * kSimds ? env.F : DevFront{nullptr, nullptr, 0};
-  if (fr.win) {
-    LIM_SWITCH(KSV, hipLaunchKernelGGL(k_lfront<KSV>, dim3(env.Z * env.I), dim3(kWave), 0,
-                                       env.stream, env.S, env.P, env.L, env.Z, env.I, t_ptr,
-                                       t_val, env.max_iters, fr))
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  LIM_SWITCH(KSV, hipLaunchKernelGGL(k_lest<KSV>, dim3((unsigned)total), dim3(kWave), 0,
-                                     env.stream, env.S, env.P, env.L, env.Z, Q, env.I,
-                                     q_prefill, t_ptr, t_val, env.max_prompt, env.reading,
-                                     env.max_iters, ttft, iters, env.err, fr))
-  return hipGetLastError();
+  if (total <= 4 * kSimds)
+    return launch_lim_est_from<false>(env, Q, q_prefill, t_ptr, t_val, ttft, iters);
+  LIM_SWITCH(KSV, hipLaunchKernelGGL(k_lfront<KSV>, dim3(env.Z * env.I), dim3(kWave), 0,
+                                     env.stream, env.S, env.P, env.L, env.Z, env.I, t_ptr,
+                                     t_val, env.max_iters, env.T))
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_lim_est_from<true>(env, Q, q_prefill, t_ptr, t_val, ttft, iters);
 }
 
 hipError_t launch_lim_commit(const LaunchEnv& env, const int32_t* choice,

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 from gpu_util import DEV, T, assert_state_equal, bits  # noqa: E402
 from oracle import oracle as O  # noqa: E402
-from paper_2607_18253_amd import context_for  # noqa: E402
+from paper_2607_18253_amd import LarContext, context_for  # noqa: E402
 from workloads import make_tiny_workload  # noqa: E402
 
 MAX_ITERS = 200_000
@@ -142,3 +142,16 @@ def test_deep_windows(name, terms):
     assert 2 * run > kw["M"] and run > 128
     print(f"limits deep windows {name} terms {terms} seed {seed}: {run} running", flush=True)
     _against_oracle(wl, int(terms))
+
+
+def test_set_scheduler_takes_no_device_memory():
+    """The context's device state is what its creation and load_state allocate; a what-if
+    call's admission points lie in it (2048 queues of 1024 sequences)."""
+    limits = np.tile(np.array([0, 0, 0, 4096], np.int32), (2048, 1))
+    ctx = LarContext(1, 2048, max_seqs_cap=1024, queue_cap=16, max_prompt=64)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for _ in range(3):
+        ctx.set_scheduler(limits)
+    assert torch.cuda.mem_get_info()[0] == free
+    ctx.close()
