@@ -521,13 +521,21 @@ hipError_t launch_lim_est(const LaunchEnv& env, int Q, const int32_t* q_prefill,
                                  int32_t* iters) {
   const int64_t total = (int64_t)env.Z * Q * env.I;
   if (total > 0x7fffffff) return hipErrorInvalidValue;
-  // The shared admission points save the repeated batches, not their latency: up to four
-  // waves per SIMD every pair still runs at once and simulates them beside the others,
-  // and a launch of its own would only come on top.  64 instances, us without and with:
-  // 32 residents each 2048 pairs 25 / 29, 4096 32 / 34, 8192 49 / 46, 15552 78 / 62; 88
-  // residents 62 / 61, 74 / 63, 118 / 70, 183 / 84.  The line is where no load loses.
-  constexpr int64_t kSimds = 1024;
-  if (total <= 4 * kSimds)
+  // The shared admission points save the batches that each of a queue's estimates would
+  // repeat, but their own launch comes before the first estimate, and below the number of
+  // waves that run side by side the repeated batches hide behind each other.  So they are
+  // used when the pairs beyond the first few of each queue are more than those waves; fewer
+  // for wide queues, whose registers and LDS leave room for fewer waves.  us from the
+  // state / from the points, light and full caches:
+  //   64 sequences, 64 instances x 96 queries 35 / 40 and 494 / 422, 600 x 16 40 / 45 and
+  //   533 / 557; 128, 64 x 96 38 / 42 and 630 / 491, 4200 x 4 74 / 81 and 567 / 591;
+  //   256, 64 x 96 45 / 46 and 412 / 333, 600 x 8 43 / 47 and 394 / 424, 4200 x 3 95 / 96
+  //   and 687 / 642; one query each of 4200 68 / 74 and 500 / 620;
+  //   512, 64 x 48 79 / 78 and 267 / 233; 1024, 64 x 24 82 / 88 and 267 / 248, 64 x 33
+  //   97 / 88 and 407 / 248.
+  const int few = env.ks == 1 ? 16 : (env.ks == 2 ? 6 : 2);
+  const int side_by_side = env.ks <= 4 ? 4096 : (env.ks == 8 ? 2048 : 1024);
+  if ((int64_t)(Q - few) * env.Z * env.I <= side_by_side)
     return launch_lim_est_from<false>(env, Q, q_prefill, t_ptr, t_val, ttft, iters);
   LIM_SWITCH(KSV, hipLaunchKernelGGL(k_lfront<KSV>, dim3(env.Z * env.I), dim3(kWave), 0,
                                      env.stream, env.S, env.P, env.L, env.Z, env.I, t_ptr,
