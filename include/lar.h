@@ -270,7 +270,8 @@ lar_status lar_commit(lar_ctx *ctx, const int32_t *choice, int32_t q_prefill, in
  *   lar_commit(choice, *q_prefill, *q_decode, *t_next_ms)
  * with the values read when the step runs.  The instances must be advanced to *t_ms
  * (the previous step's *t_next_ms, or lar_commit(NULL, ...) before the first step).
- * Enqueues four kernels; allocates nothing, does not synchronise.
+ * Enqueues two kernels (with n_scen * n_inst >= 4096 four, three under scheduler limits);
+ * allocates nothing, does not synchronise.
  *   q_prefill, q_decode dev [1] int32;  t_ms, t_next_ms dev [1]
  *   acc, cost dev [n_cols] (this query's row);  w_cost dev [Z]
  *   w_lat dev [Z] (Lagrangian objective) or tau_ms dev [1] (Eq. 3; w_lat unused)

@@ -155,8 +155,8 @@ __device__ __forceinline__ void step_estimate(const DevParams& pr, const DevTraj
 // STEP: a routing step's first launch; the one query's estimate follows from the
 // trajectory in the same wave, which reads back what its own lane 0 stored (made visible
 // by the fence), so the walk is the what-if's.  With the route in the commit
-// (k_commit<KS, true>) a step is two launches instead of four:
-// 4 instances, a step from the host 17.0 -> 11.4 us, its kernels 12.3 -> 10.2 us.
+// (k_commit<KS, true>) a step of fewer than 4096 queues is two launches instead of four
+// (see launch_step).
 template <int KS, bool NC, bool STEP>
 __global__ __launch_bounds__(kWave) void k_traj(DevState S, DevParams pr, DevTraj tr, int Z, int I,
                                                const double* t_ptr, double t_val,
@@ -2022,6 +2022,23 @@ hipError_t launch_commit(const LaunchEnv& env, const int32_t* choice, int64_t ch
 }
 
 hipError_t launch_step(const LaunchEnv& env, const StepArgs& a) {
+  // Two launches save the time between launches, but one lane of each trajectory wave
+  // estimates, and every commit wave routes its scenario's row, I^2 candidates a scenario.
+  // From 4096 queues on that costs more: us for 24 steps in two / in four launches,
+  // 1024 instances 556 / 597, 3072 1106 / 1145, 4096 1520 / 1457, 8192 4083 / 2572; 512 x 8
+  // scenarios 818 / 848, 256 x 32 1169 / 1118, 32 x 4096 9942 / 7977.  Under limits (two /
+  // three), 16 steps, 2048 612 / 632, 4096 1060 / 1042.
+  constexpr int64_t kFused = 4096;
+  if ((int64_t)env.Z * env.I >= kFused) {
+    hipError_t e = launch_traj(env, a.t, 0.0);
+    if (e == hipSuccess) e = launch_est(env, 1, a.qp, a.t, 0.0, a.row_ttft, nullptr);
+    // (one row a scenario: n_cols is not used)
+    if (e == hipSuccess)
+      e = launch_route(env, 1, a.row_ttft, (int64_t)env.I, a.acc, a.cost, 0, a.w_cost, a.w_lat,
+                       a.tau, a.choice, a.chosen_ttft, a.utility, 1, 0);
+    if (e == hipSuccess) e = launch_commit(env, a.choice, 1, a.qp, a.qd, 0, 0, a.t_next, 0.0);
+    return e;
+  }
   const StepRow sr{a.row_ttft, a.acc, a.cost, a.w_cost, a.w_lat, a.tau, a.choice,
                    a.chosen_ttft, a.utility};
   if (env.limited) {

@@ -1,5 +1,5 @@
-"""Routing steps of large pools: two launches whatever the pool's size, and the same
-results as the oracle's."""
+"""Routing steps on both sides of the pool size where their launches change: as many
+launches as documented, and the oracle's results."""
 
 from __future__ import annotations
 
@@ -18,6 +18,7 @@ from gpu_util import DEV, T, assert_state_equal, bits  # noqa: E402
 from oracle import oracle as O  # noqa: E402
 from paper_2607_18253_amd import context_for  # noqa: E402
 from paper_2607_18253_amd.lar import LIB_PATH  # noqa: E402
+from workloads import make_tiny_workload  # noqa: E402
 from workloads.gen import make_tiny_sched_workload  # noqa: E402
 
 F64, I32 = torch.float64, torch.int32
@@ -71,13 +72,18 @@ def _launches(ctx, b, s):
     return n.value
 
 
-@pytest.mark.parametrize("n_inst", [5, 4100])
-def test_limited_step_starts_from_the_state(n_inst):
-    """One query per queue shares nothing: no launch for admission points, for any pool."""
-    wl = make_tiny_sched_workload(31, n_inst=n_inst, n_q=4, max_res=6)
-    print(f"limited steps: {n_inst} instances", flush=True)
+# Below 4096 queues the estimate follows the trajectory and the route precedes the commit in
+# the same launch; from there on each has its own.  Under limits there is no trajectory, and
+# one query per queue shares nothing: no launch for admission points, for any pool.
+@pytest.mark.parametrize("limits", [False, True])
+@pytest.mark.parametrize("n_inst,n_scen", [(5, 1), (4095, 1), (4096, 1), (4100, 1), (2048, 2)])
+def test_step_launches(n_inst, n_scen, limits):
+    make = make_tiny_sched_workload if limits else make_tiny_workload
+    wl = make(31 + n_inst, n_inst=n_inst, n_q=4, max_res=6, n_scen=n_scen)
+    print(f"steps: {n_inst} instances, {n_scen} scenarios, limits {limits}", flush=True)
     s = torch.cuda.Stream()
     ctx = context_for(wl, max_iters=200_000, stream=s)
     b = _steps_against_oracle(wl, ctx, s)
-    assert _launches(ctx, b, s) == 2
+    fused = n_inst * n_scen < 4096
+    assert _launches(ctx, b, s) == (2 if fused else (3 if limits else 4))
     ctx.close()
