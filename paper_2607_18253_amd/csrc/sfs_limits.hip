@@ -154,11 +154,9 @@ __global__ __launch_bounds__(kWave) void k_lfront(DevState S, DevParams pr, DevL
   int64_t n = 0;
   // (a state behind t and a batch cap that ends the search are errors only once a query
   // is estimated: the estimates then start from the state and report them)
-  if (w.clock < t || !lim_frontier(w, e, n, max_iters)) {
-    w.template load<false>(S, e, qid, nullptr);
-    n = 0;
-  }
-  w.to_front(S, fr, qid, n);
+  LQueue<KS> g = w;
+  if (!(w.clock < t) && lim_frontier(g, e, n, max_iters)) g.to_front(S, fr, qid, n);
+  else w.to_front(S, fr, qid, 0);
 }
 
 // What-if estimates under limits: one wave per (scenario, query, instance), instance
