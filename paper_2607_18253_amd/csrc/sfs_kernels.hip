@@ -1935,6 +1935,12 @@ static hipError_t launch_trace_ks(const LaunchEnv& env, const TraceArgs& a) {
     constexpr int W = KS <= 4 ? 16 : 8;
     if (fits(W)) return launch_trace_parts<KS, W>(env, a, kCus);
   } else {
+    // One or two instances: a workgroup of as many waves, five and two of which share a CU
+    // (in 4-wave workgroups, whose LDS one scenario fills, 1024 scenarios of one instance,
+    // 64 queries, 6.1 ms with short queues and 12.8 with long ones; with the states in HBM
+    // 2.5 and 37.0; in 1-wave workgroups 2.5 and 4.6).
+    if (env.I == 1 && fits(1)) return launch_trace_parts<KS, 1>(env, a, kCus);
+    if (env.I == 2 && fits(2)) return launch_trace_parts<KS, 2>(env, a, kCus);
     if (fits(4)) return launch_trace_parts<KS, 4>(env, a, kCus);
   }
   // Otherwise the states stay in HBM (L2) and are loaded per use.

@@ -93,3 +93,18 @@ def test_trace_parts_captured(n_inst, n_scen, mcap):
         assert torch.equal(chosen.view(torch.int64), want[1].view(torch.int64))
     ctx.sync()
     ctx.close()
+
+
+@pytest.mark.parametrize("n_inst,n_scen", [(1, 1), (1, 1300), (2, 2), (2, 600)])
+def test_trace_one_or_two_wide_instances(n_inst, n_scen):
+    """Up to 1024 sequences on one or two instances: workgroups of as many waves."""
+    wl = make_tiny_workload(60 + n_inst, n_inst=n_inst, max_res=40, n_q=70, n_scen=n_scen,
+                            max_seqs=(1, 600), budget=(1, 900))
+    choice, chosen, util, ctx = gpu_trace(wl, queue_cap=256, max_seqs_cap=1000)
+    for z in sorted({0, n_scen - 1} | set(range(0, n_scen, 97))):
+        ref = O.trace(wl, scenario=z, queue_cap=256)
+        np.testing.assert_array_equal(choice[z], ref.choice, err_msg=f"scenario {z}")
+        np.testing.assert_array_equal(bits(chosen[z]), bits(ref.ttft_chosen))
+        np.testing.assert_array_equal(bits(util[z]), bits(ref.util_chosen))
+        assert_state_equal(ctx, z, O.trace(wl, scenario=z, queue_cap=256, final_state=True))
+    ctx.close()

@@ -81,3 +81,13 @@ def test_limits_traces_share_a_cu(kernels, slots, per_cu):
         vgprs = -(-k[".vgpr_count"] // 8) * 8 + -(-k.get(".agpr_count", 0) // 8) * 8
         assert vgprs * per_cu <= 512, n
         assert k[".group_segment_fixed_size"] * per_cu <= 160 * 1024, n
+
+
+@pytest.mark.parametrize("waves,per_cu", [(1, 5), (2, 2)])
+def test_wide_traces_of_few_instances_share_a_cu(kernels, waves, per_cu):
+    """A trace of one or two instances of up to 1024 sequences holds the LDS of its own
+    waves, so that several scenarios share a CU."""
+    names = [n for n in kernels if f"10k_trace_clILi16ELi{waves}ELi1E" in n]
+    assert len(names) == 2
+    for n in names:
+        assert kernels[n][".group_segment_fixed_size"] * per_cu <= 160 * 1024, n
