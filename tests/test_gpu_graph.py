@@ -6,6 +6,7 @@ synchronisation between replays."""
 
 from __future__ import annotations
 
+import ctypes
 import os
 import sys
 
@@ -16,10 +17,12 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
-from gpu_util import assert_state_equal, bits  # noqa: E402
+from gpu_util import T, assert_state_equal, bits  # noqa: E402
 from oracle import oracle as O  # noqa: E402
 from paper_2607_18253_amd import context_for  # noqa: E402
+from paper_2607_18253_amd.lar import LIB_PATH  # noqa: E402
 from workloads import make_workload  # noqa: E402
+from workloads.gen import make_tiny_sched_workload  # noqa: E402
 
 
 @pytest.mark.parametrize("objective,workload", [("lagrangian", "c2"), ("constrained", "c2"),
@@ -67,4 +70,56 @@ def test_route_step_graph_replays(objective, workload):
         assert bits(chosen.cpu().numpy())[0] == bits(ref.ttft_chosen[i:i + 1])[0], i
     ctx.sync()
     assert_state_equal(ctx, 0, ref)
+    ctx.close()
+
+
+class _KernelNode(ctypes.Structure):
+    """hipKernelNodeParams."""
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p),
+                ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def _grids(g):
+    """Workgroups of each kernel node of a captured graph."""
+    lib = ctypes.CDLL(LIB_PATH)   # finds the runtime that the library itself is linked with
+    n = ctypes.c_size_t(0)
+    raw = ctypes.c_void_p(g.raw_cuda_graph())
+    assert lib.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert lib.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = _KernelNode()
+        assert lib.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append(p.grid[0] * p.grid[1] * p.grid[2])
+    return out
+
+
+def test_captured_trace_never_waits_for_what_is_not_resident():
+    """A trace under limits whose workgroups the device does not hold at once (600 scenarios,
+    two workgroups of four wide queues each): the capture, too, takes the kernel whose
+    workgroups wait for none, one per scenario.  Checked before the graph runs."""
+    Z = 600
+    wl = make_tiny_sched_workload(77, n_inst=5, n_q=6, max_res=5, n_scen=Z)
+    s = torch.cuda.Stream()
+    ctx = context_for(wl, stream=s, max_iters=200_000, max_seqs_cap=300)
+    args = (T(wl.q_prefill, torch.int32), T(wl.q_decode, torch.int32),
+            T(wl.q_t_ms, torch.float64), float(wl.q_t_ms[-1]), T(wl.acc, torch.float64),
+            T(wl.cost, torch.float64), T(wl.w_cost, torch.float64), T(wl.w_lat_ms, torch.float64))
+    choice = torch.zeros((Z, wl.n_q), dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        ctx.advance(float(wl.q_t_ms[0]))
+    s.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g, stream=s):
+        ctx.route_trace(*args, choice=choice)
+    assert _grids(g)[-1] == Z
+    with torch.cuda.stream(s):
+        g.replay()
+    ctx.sync()
+    for z in range(0, Z, 59):
+        ref = O.trace(wl, scenario=z, max_iters=200_000)
+        np.testing.assert_array_equal(choice[z].cpu().numpy(), ref.choice)
     ctx.close()
