@@ -99,7 +99,8 @@ typedef struct {
  * other workgroups (default 10000 ms, then LAR_E_SYNC); LAR_TEST_SKIP_POST=m:q makes
  * workgroup m of every scenario skip its post for query q (so the others reach the
  * bound); LAR_TEST_TAG_START starts the realised-TTFT tag counter at that value (so
- * a test reaches its wrap).
+ * a test reaches its wrap); LAR_TEST_CUS takes the device to have that many CUs (so a
+ * test reaches trace launches that are small, or refused and halved).
  */
 lar_status lar_create(lar_ctx **out, const lar_config *cfg);
 

@@ -31,6 +31,7 @@ struct lar_ctx {
   int32_t* pi = nullptr;  // [3][I]: B, M, col
   double* row_ttft = nullptr;  // [Z][I] TTFT row of lar_route_step
   uint64_t* xslot = nullptr;   // [Z][2][kMaxCluster][4] candidate posts of the clustered trace
+  int cus = 0;                 // CUs of the device
   lar::SyncCtl sync{1000000000ull, -1, -1};   // 10 s wait bound; no post left out
   unsigned long long* work = nullptr;          // [Z] estimate batches of the last trace
   double* lps_wait = nullptr;                  // [Z][I] LPS queueing delays (lar_estimate_lps)
@@ -115,6 +116,7 @@ LaunchEnv env_of(const lar_ctx* ctx) {
   e.sync = ctx->sync;
   e.work = ctx->work;
   e.limited = ctx->limited;
+  e.cus = ctx->cus;
   e.L.H = ctx->plim;
   e.L.K = ctx->plim + ctx->I;
   e.L.sh = ctx->plim + 2 * ctx->I;
@@ -215,9 +217,19 @@ lar_status lar_create(lar_ctx** out, const lar_config* cfg) {
     st = fail(ctx, LAR_E_HIP, "hipMemset of the error word failed");
   if (st == LAR_OK && hipMemset(ctx->work, 0, sizeof(unsigned long long) * ctx->Z) != hipSuccess)
     st = fail(ctx, LAR_E_HIP, "hipMemset of the work counters failed");
+  int dev = 0;
+  if (st == LAR_OK &&
+      (hipGetDevice(&dev) != hipSuccess ||
+       hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess))
+    st = fail(ctx, LAR_E_HIP, "device properties not available");
   if (st != LAR_OK) {
     lar_destroy(ctx);
     return st;
+  }
+  // Test hook of the traces' launches: LAR_TEST_CUS sets the CUs a device is taken to have.
+  if (const char* v = std::getenv("LAR_TEST_CUS")) {
+    const long long n = std::atoll(v);
+    if (n > 0 && n <= 1 << 20) ctx->cus = (int)n;
   }
   ctx->T.K = 0;
   *out = ctx;

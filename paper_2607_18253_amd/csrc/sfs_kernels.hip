@@ -1888,22 +1888,28 @@ static hipError_t launch_trace_mem_any(const LaunchEnv& env, const TraceArgs& a)
 // number of them.  225 scenarios x 30 instances, 1000 queries: 10.6 ms in two launches
 // against 77 ms with the states in HBM, where every estimate reloads its queue and walks
 // the whole backlog again; 24 instances of up to 1024 sequences, 1500 queries: 16.6
-// against 860 ms.  wgs: workgroups the device holds at once.  A launch that the
-// runtime refuses runs its scenarios on the HBM-state kernel.
+// against 860 ms.  A part starts with as many scenarios as the CUs hold, one workgroup
+// each; a device that holds fewer (CUs masked or in use) refuses it, and it is halved down
+// to one scenario before the HBM-state kernel takes it.
 template <int KS, int W>
-static hipError_t launch_trace_parts(const LaunchEnv& env, const TraceArgs& a, int wgs) {
+static hipError_t launch_trace_parts(const LaunchEnv& env, const TraceArgs& a) {
   const int G = (env.I + W - 1) / W;
-  const int per = G == 1 ? env.Z : (wgs > G ? wgs / G : 1);
-  const int parts = (env.Z + per - 1) / per;
-  for (int k = 0; k < parts; ++k) {
-    const int z0 = (int)((int64_t)env.Z * k / parts);
-    const int z1 = (int)((int64_t)env.Z * (k + 1) / parts);
+  int per = G == 1 ? env.Z : (env.cus > G ? env.cus / G : 1);
+  for (int z0 = 0; z0 < env.Z;) {
+    const int left = env.Z - z0;
+    const int parts = (left + per - 1) / per;
+    const int n = (left + parts - 1) / parts;   // parts of about equal size
     LaunchEnv ek = env;
     TraceArgs ak = a;
-    slice_scenarios(ek, ak, z0, z1 - z0);
+    slice_scenarios(ek, ak, z0, n);
     hipError_t e = launch_trace_cl<KS, W, 1>(ek, ak);
+    if (e == hipErrorInvalidConfiguration && n > 1) {
+      per = (n + 1) / 2;
+      continue;
+    }
     if (e == hipErrorInvalidConfiguration) e = launch_trace_mem_any<KS>(ek, ak);
     if (e != hipSuccess) return e;
+    z0 += n;
   }
   return hipSuccess;
 }
@@ -1915,7 +1921,10 @@ static hipError_t launch_trace_ks(const LaunchEnv& env, const TraceArgs& a) {
   // queues get one wave per SIMD (4 per workgroup; the per-query chain is issue
   // latency bound, so a wave runs fastest alone on its SIMD), more get 16-wave
   // workgroups (4 waves per SIMD, 128 VGPRs each; KS = 8: 8 waves), one per CU, in as
-  // many launches as that takes.  KS = 16 keeps 4 waves (their states fill 110 KiB of
+  // many launches as that takes.  Pools of up to four instances take 4-wave workgroups
+  // however many their scenarios: no workgroup waits for another, and a CU holds several
+  // (4 instances x 1024 scenarios, 100 queries, 1.6 ms against 2.8 in 16-wave workgroups).
+  // KS = 16 keeps 4 waves (their states fill 110 KiB of
   // LDS, one workgroup per CU).  N must fit the 31-bit post tags
   // and the decode-only tail of an estimate (at most K batches) one lane per batch.
   const int64_t queues = (int64_t)env.Z * env.I;
@@ -1924,7 +1933,6 @@ static hipError_t launch_trace_ks(const LaunchEnv& env, const TraceArgs& a) {
     return G <= kMaxCluster && (uint64_t)a.N < (1ull << 31) && env.T.K >= 1 &&
            env.T.K <= kWave;
   };
-  constexpr int kCus = 256;
   // A shape whose workgroups the runtime cannot make resident together reports
   // hipErrorInvalidConfiguration without running; the next one is tried, and the
   // HBM-state kernel, whose workgroups never wait for each other, takes any size.
@@ -1933,15 +1941,15 @@ static hipError_t launch_trace_ks(const LaunchEnv& env, const TraceArgs& a) {
     if ((queues <= 1024 || env.I <= 4) && fits(4)) e = launch_trace_cl<KS, 4, 1>(env, a);
     if (e != hipErrorInvalidConfiguration) return e;
     constexpr int W = KS <= 4 ? 16 : 8;
-    if (fits(W)) return launch_trace_parts<KS, W>(env, a, kCus);
+    if (fits(W)) return launch_trace_parts<KS, W>(env, a);
   } else {
     // One or two instances: a workgroup of as many waves, five and two of which share a CU
     // (in 4-wave workgroups, whose LDS one scenario fills, 1024 scenarios of one instance,
     // 64 queries, 6.1 ms with short queues and 12.8 with long ones; with the states in HBM
     // 2.5 and 37.0; in 1-wave workgroups 2.5 and 4.6).
-    if (env.I == 1 && fits(1)) return launch_trace_parts<KS, 1>(env, a, kCus);
-    if (env.I == 2 && fits(2)) return launch_trace_parts<KS, 2>(env, a, kCus);
-    if (fits(4)) return launch_trace_parts<KS, 4>(env, a, kCus);
+    if (env.I == 1 && fits(1)) return launch_trace_parts<KS, 1>(env, a);
+    if (env.I == 2 && fits(2)) return launch_trace_parts<KS, 2>(env, a);
+    if (fits(4)) return launch_trace_parts<KS, 4>(env, a);
   }
   // Otherwise the states stay in HBM (L2) and are loaded per use.
   return launch_trace_mem_any<KS>(env, a);

@@ -39,6 +39,7 @@ struct LaunchEnv {
   // scheduler limits: when set, estimates, commits and traces run the explicit-list
   // engine of sfs_limits.h on the state laid out for it
   bool limited;
+  int cus;            // CUs of the device
   DevLimits L;
 };
 

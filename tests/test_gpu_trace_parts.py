@@ -108,3 +108,40 @@ def test_trace_one_or_two_wide_instances(n_inst, n_scen):
         np.testing.assert_array_equal(bits(util[z]), bits(ref.util_chosen))
         assert_state_equal(ctx, z, O.trace(wl, scenario=z, queue_cap=256, final_state=True))
     ctx.close()
+
+
+# launches of a trace: the work counters' clear, then per part its exchange's clear and its
+# kernel; a refused part leaves its clear
+@pytest.mark.parametrize("cus,n_scen,launches", [
+    (9, 64, 1 + 2 * 16), (3, 64, 1 + 2 * 64), (1, 62, 1 + 2 * 62), (4096, 131, 1 + 1 + 2 * 2)])
+def test_trace_parts_follow_the_device(monkeypatch, cus, n_scen, launches):
+    """The parts of a trace are as large as the device holds at once: fewer CUs, smaller
+    parts; where it holds less than its CUs say (here: is taken to have more CUs than it
+    has), a refused part is halved instead of leaving the chip."""
+    import ctypes
+    from gpu_util import T
+    from paper_2607_18253_amd import context_for
+    from paper_2607_18253_amd.lar import LIB_PATH
+    monkeypatch.setenv("LAR_TEST_CUS", str(cus))
+    wl = make_tiny_workload(90 + cus, n_inst=17, max_res=4, n_q=10, n_scen=n_scen)
+    print(f"trace parts: {cus} CUs, {n_scen} scenarios", flush=True)
+    choice, chosen, util, ctx = gpu_trace(wl, queue_cap=64)
+    for z in sorted({0, n_scen - 1} | set(range(0, n_scen, 13))):
+        ref = O.trace(wl, scenario=z, queue_cap=64)
+        np.testing.assert_array_equal(choice[z], ref.choice, err_msg=f"scenario {z}")
+        np.testing.assert_array_equal(bits(chosen[z]), bits(ref.ttft_chosen))
+    ctx.close()
+    s = torch.cuda.Stream()
+    ctx = context_for(wl, stream=s, queue_cap=64)
+    args = (T(wl.q_prefill, torch.int32), T(wl.q_decode, torch.int32),
+            T(wl.q_t_ms, torch.float64), float(wl.q_t_ms[-1]), T(wl.acc, torch.float64),
+            T(wl.cost, torch.float64), T(wl.w_cost, torch.float64), T(wl.w_lat_ms, torch.float64))
+    out = torch.zeros((n_scen, wl.n_q), dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g, stream=s):
+        ctx.route_trace(*args, choice=out)
+    lib, n = ctypes.CDLL(LIB_PATH), ctypes.c_size_t(0)
+    assert lib.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    assert n.value == launches
+    ctx.close()
