@@ -1898,7 +1898,7 @@ static hipError_t launch_trace_parts(const LaunchEnv& env, const TraceArgs& a) {
   for (int z0 = 0; z0 < env.Z;) {
     const int left = env.Z - z0;
     const int parts = (left + per - 1) / per;
-    const int n = (left + parts - 1) / parts;   // parts of about equal size
+    const int n = left / parts;   // parts of about equal size
     LaunchEnv ek = env;
     TraceArgs ak = a;
     slice_scenarios(ek, ak, z0, n);

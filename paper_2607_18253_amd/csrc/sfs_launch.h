@@ -116,24 +116,30 @@ hipError_t launch_stats(const LaunchEnv& env, int N, const int32_t* choice,
 // Launch a grid whose workgroups wait for each other (the clustered traces: the
 // members of a scenario exchange candidates every query) as a cooperative launch,
 // so that the runtime either makes every workgroup resident at once or refuses the
-// launch.  A stream capture records the launch without that check, so the grid is held
-// against the device here first.  A refusal is reported as hipErrorInvalidConfiguration, on
-// which the callers fall through to a launch shape that needs no co-residency.  The kernel's
-// bounded wait stays as a backstop.
+// launch.  A stream capture records the launch without that check, so there the grid is
+// held against the device first (about 35 us a launch, which eager launches need not pay).
+// A refusal is reported as hipErrorInvalidConfiguration, on which the callers fall through
+// to a launch shape that needs no co-residency.  The kernel's bounded wait stays as a
+// backstop.
 template <typename... KArgs, typename... Args>
 inline hipError_t launch_together(void (*kernel)(KArgs...), dim3 grid, dim3 block,
                                   hipStream_t stream, Args... args) {
   static_assert(sizeof...(KArgs) == sizeof...(Args), "one value per kernel parameter");
-  int dev = 0, cus = 0, per_cu = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess)
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, reinterpret_cast<const void*>(kernel), (int)(block.x * block.y * block.z), 0);
+  hipError_t e = hipSuccess;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (stream) e = hipStreamIsCapturing(stream, &capture);
+  if (e == hipSuccess && capture != hipStreamCaptureStatusNone) {
+    int dev = 0, cus = 0, per_cu = 0;
+    e = hipGetDevice(&dev);
+    if (e == hipSuccess)
+      e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess)
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+          &per_cu, reinterpret_cast<const void*>(kernel), (int)(block.x * block.y * block.z), 0);
+    if (e == hipSuccess && (int64_t)grid.x * grid.y * grid.z > (int64_t)per_cu * cus)
+      return hipErrorInvalidConfiguration;
+  }
   if (e != hipSuccess) return e;
-  if ((int64_t)grid.x * grid.y * grid.z > (int64_t)per_cu * cus)
-    return hipErrorInvalidConfiguration;
   std::tuple<KArgs...> vals(static_cast<KArgs>(args)...);
   void* ptrs[sizeof...(KArgs)];
   std::apply([&ptrs](auto&... v) {

@@ -290,9 +290,9 @@ __global__ __launch_bounds__(NW * kWave) void k_ltrace(LAR_TRACE_PARAMS, DevLimi
 // workgroup's best candidate (LDS), the exchange with the other members, the outputs
 // from the wave holding the winner, then every wave commits i and replays its
 // instance to the next arrival and estimates query i + 1 from the instance's cached
-// admission point (lim_frontier), which stays valid while the instance receives no
-// query and its replay has not passed that point.  TRK: the replay reports realised
-// TTFT.
+// admission point (lim_frontier), which stays valid while its replay has not passed that
+// point; a query that the instance receives before then joins it, and the search for the
+// next point goes on from there.  TRK: the replay reports realised TTFT.
 //
 // Registers are bounded so that 4, 4, 3 and 2 workgroups (KS = 1, 2, 4, 8) share a CU:
 // unbounded the compiler takes 144, 160, 194 and 236, and pools that the device no longer
@@ -389,10 +389,10 @@ __global__ __launch_bounds__(W * kWave, lim_trace_per_cu<KS>()) void k_ltrace_cl
       if (own) {
         const bool taken = lim_commit_advance<KS, TRK>(Q, e, j == m, p, dq, tn, S.qcap,
                                                        max_iters, err, tags, tag0 + i, tk);
-        // F stays the admission point while the replay has not run its batch and the
-        // instance receives no query.  A query it receives waits until F: it joins the
-        // copy there, and the search for the next point goes on from F, so that each
-        // batch is searched once and not again for every query that joins behind it.
+        // F stays the admission point while the replay has not run its batch.  A query
+        // that the instance receives waits until F: it joins the copy there, and the
+        // search for the next point goes on from F, so that each batch is searched once
+        // and not again for every query that joins behind it.
         if (j == m) {
           if (f_ok && taken) F.join(p, entry_decode(e, p, dq));
           f_on = f_ok && taken ? 1 : 0;
