@@ -28,11 +28,11 @@
 // the context of the decoding requests are carried from batch to batch, and in QScal
 // from one kernel to the next.  Chunks and admissions are saturating DPP prefix sums
 // over the rows that hold any; a batch that must preempt pops its victims one by one.
-// Batches that repeat the one before are folded (LQueue::fold).  One wave per SIMD runs at the
-// latency of its dependent instructions, so their number is the engine's time.  Against
+// Batches that repeat the one before are folded (LQueue::fold).  One wave per SIMD runs at
+// the latency of its dependent instructions, so their number is the engine's time.  Against
 // wave sums for every count and one lane walking lists in LDS to preempt (and without the
 // shared and carried admission points of sfs_limits.hip), of 256 sequences each: 27
-// instances x 243 queries 534 -> 331 us; 32 instances, 2500 queries 132 -> 91 ms; of 1024
+// instances x 243 queries 534 -> 339 us; 32 instances, 2500 queries 132 -> 91 ms; of 1024
 // each, 32 x 100 1.59 -> 1.21 ms.
 #pragma once
 
