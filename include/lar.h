@@ -278,8 +278,7 @@ lar_status lar_commit(lar_ctx *ctx, const int32_t *choice, int32_t q_prefill, in
  *   w_lat dev [Z] (Lagrangian objective) or tau_ms dev [1] (Eq. 3; w_lat unused)
  *   choice dev [Z] int32;  chosen_ttft, utility dev [Z] (may be NULL)
  * Device-found errors (prompt outside 1..max_prompt, queue full, iteration cap) are
- * sticky as for the separate calls; when one step finds errors of different kinds, which
- * of them is reported is not fixed.
+ * sticky as for the separate calls.
  */
 lar_status lar_route_step(lar_ctx *ctx, const int32_t *q_prefill, const int32_t *q_decode,
                           const double *t_ms, const double *t_next_ms, const double *acc,

@@ -77,17 +77,23 @@ struct EstBack {
     return __dadd_rn(__dadd_rn(t, td), te);
   }
   // TTFT of a query of p prompt tokens that arrives at t; it_out: its batches (-1 when
-  // it has no estimate: NaN, with the error set).
+  // it has no estimate: NaN, with the error set).  DEFER: an error goes to *err as it is,
+  // a word of this queue's own.
+  template <bool DEFER>
   __device__ __forceinline__ double query(const DevTraj& tr, int qid, int ZI, int p, double t,
                                           int max_prompt, int reading, int64_t max_iters,
                                           int32_t* err, int32_t* it_out) const {
+    auto report = [&](int code) {
+      if constexpr (DEFER) *err = code;
+      else set_error(err, code);
+    };
     *it_out = -1;
     if (p < 1 || p > max_prompt) {
-      set_error(err, kErrArg);
+      report(kErrArg);
       return __builtin_nan("");
     }
     if (!ok) {
-      set_error(err, kErrIter);   // a clock behind t was already reported as a state error
+      report(kErrIter);   // a clock behind t was already reported as a state error
       return __builtin_nan("");
     }
     int64_t it = it0;
@@ -101,7 +107,7 @@ struct EstBack {
     int kk = 0;
     while (!done) {
       if (kk >= K) {   // cannot happen for p <= max_prompt; guard the tail bounds
-        set_error(err, kErrIter);
+        report(kErrIter);
         E = __builtin_nan("");
         break;
       }
@@ -122,14 +128,15 @@ struct EstBack {
       ++kk;
       ++it;
     }
-    if (it > max_iters) set_error(err, kErrIter);
+    if (it > max_iters) report(kErrIter);
     *it_out = (int32_t)it;
     return __dsub_rn(E, t);
   }
 };
 
 // The one query of a routing step, and its estimate in the wave that has just stored
-// queue qid's trajectory.
+// queue qid's trajectory.  Its errors are left in the queue's ok word for the commit to
+// report: every queue's state errors come before any estimate's, as in separate launches.
 struct StepQuery {
   const int32_t* p;
   int max_prompt, reading;
@@ -137,15 +144,16 @@ struct StepQuery {
 };
 __device__ __forceinline__ void step_estimate(const DevParams& pr, const DevTraj& tr, int qid,
                                               int j, int ZI, double t, int64_t max_iters,
-                                              int32_t* err, const StepQuery& sq) {
+                                              const StepQuery& sq) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   if (lane_id() == 0) {
     EstBack b;
     b.load(pr, tr, qid, j);
-    int32_t it;
-    sq.ttft[qid] =
-        b.query(tr, qid, ZI, *sq.p, t, sq.max_prompt, sq.reading, max_iters, err, &it);
+    int32_t it, code = 0;
+    sq.ttft[qid] = b.query<true>(tr, qid, ZI, *sq.p, t, sq.max_prompt, sq.reading, max_iters,
+                                 &code, &it);
+    tr.ok[qid] = code;   // (0: none; error codes are negative)
   }
 }
 
@@ -185,7 +193,7 @@ __global__ __launch_bounds__(kWave) void k_traj(DevState S, DevParams pr, DevTra
                                                         walk_lds);
   }
   if (walked) {
-    if constexpr (STEP) step_estimate(pr, tr, qid, j, Z * I, t, max_iters, err, sq);
+    if constexpr (STEP) step_estimate(pr, tr, qid, j, Z * I, t, max_iters, sq);
     return;
   }
   // the engine, for queues outside what the walk covers
@@ -254,7 +262,7 @@ __global__ __launch_bounds__(kWave) void k_traj(DevState S, DevParams pr, DevTra
       tr.tailC[(int64_t)kk * ZI + qid] = C;
     }
   }
-  if constexpr (STEP) step_estimate(pr, tr, qid, j, Z * I, t, max_iters, err, sq);
+  if constexpr (STEP) step_estimate(pr, tr, qid, j, Z * I, t, max_iters, sq);
 }
 
 // ------------------------------------------------------------------ k_est
@@ -290,7 +298,7 @@ __global__ __launch_bounds__(256) void k_est(DevParams pr, DevTraj tr, int Z, in
   for (int q = q0; q < q1; ++q) {
     const int64_t o = ((int64_t)z * Q + q) * I + j;
     int32_t it;
-    ttft[o] = b.query(tr, qid, ZI, s_p[q - q0], t, max_prompt, reading, max_iters, err, &it);
+    ttft[o] = b.query<false>(tr, qid, ZI, s_p[q - q0], t, max_prompt, reading, max_iters, err, &it);
     if (iters) iters[o] = it;
   }
 }
@@ -437,7 +445,7 @@ __global__ __launch_bounds__(kWave) void k_commit(DevState S, DevParams pr, int 
   Queue<KS> w;
   w.load(S, e, qid);
   bool chosen;
-  if constexpr (STEP) chosen = step_route(sr, I, z, j, pr.col, err) == j;
+  if constexpr (STEP) chosen = step_route(sr, I, z, j, qid, pr.col, err) == j;
   else chosen = choice && choice[(int64_t)z * choice_zstride] == j;
   const int p = qp_ptr ? *qp_ptr : qp_val;
   const int d = qd_ptr ? *qd_ptr : qd_val;
@@ -2053,8 +2061,8 @@ hipError_t launch_step(const LaunchEnv& env, const StepArgs& a) {
     if (e == hipSuccess) e = launch_commit(env, a.choice, 1, a.qp, a.qd, 0, 0, a.t_next, 0.0);
     return e;
   }
-  const StepRow sr{a.row_ttft, a.acc, a.cost, a.w_cost, a.w_lat, a.tau, a.choice,
-                   a.chosen_ttft, a.utility};
+  const StepRow sr{env.limited ? nullptr : env.T.ok, a.row_ttft, a.acc, a.cost, a.w_cost,
+                   a.w_lat, a.tau, a.choice, a.chosen_ttft, a.utility};
   if (env.limited) {
     const hipError_t e = launch_lim_est(env, 1, a.qp, a.t, 0.0, a.row_ttft, nullptr);
     return e == hipSuccess ? launch_lim_step_commit(env, a, sr) : e;

@@ -73,6 +73,7 @@ struct StepArgs {
 
 // What the route inside a step's commit kernel reads and writes.
 struct StepRow {
+  const int32_t* est_err;   // [Z][I] errors of the estimates (0: none), or nullptr
   const double *ttft, *acc, *cost;
   const double *w_cost, *w_lat, *tau;
   int32_t* choice;

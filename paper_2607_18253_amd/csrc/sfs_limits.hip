@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kWave) void k_lcommit(DevState S, DevParams pr, Dev
   LQueue<KS> w;
   w.template load<false>(S, e, qid, nullptr);
   bool chosen;
-  if constexpr (STEP) chosen = step_route(sr, I, z, j, pr.col, err) == j;
+  if constexpr (STEP) chosen = step_route(sr, I, z, j, qid, pr.col, err) == j;
   else chosen = choice && choice[(int64_t)z * choice_zstride] == j;
   const int p = qp_ptr ? *qp_ptr : qp_val;
   const int d = qd_ptr ? *qd_ptr : qd_val;

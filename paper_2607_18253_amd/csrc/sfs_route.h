@@ -153,15 +153,22 @@ __device__ __forceinline__ void row_outputs(int bj, int64_t o, const double* tro
 }
 
 // A routing step's route inside its commit kernel, in the wave of scenario z's instance
-// j: the chosen instance (-1: none); instance 0's wave writes the outputs.
-__device__ __forceinline__ int step_route(const StepRow& s, int I, int z, int j,
+// j (queue qid): the chosen instance (-1: none); instance 0's wave writes the outputs.
+// Every wave reports its estimate's error, then a row without a candidate, before it can
+// find one in its commit.
+__device__ __forceinline__ int step_route(const StepRow& s, int I, int z, int j, int qid,
                                           const int32_t* col, int32_t* err) {
+  if (s.est_err && lane_id() == 0) {
+    const int code = s.est_err[qid];
+    if (code != 0) set_error(err, code);
+  }
   const double wc = s.w_cost[z];
   const double* trow = s.ttft + (int64_t)z * I;
   const int bj = row_best(I, trow, s.acc, s.cost, col, wc, s.w_lat[z], s.tau,
                           s.tau ? s.tau[0] : 0.0);
   if (j == 0 && lane_id() == 0)
     row_outputs(bj, z, trow, s.acc, s.cost, col, wc, s.choice, s.chosen_ttft, s.utility, err);
+  else if (bj < 0 && lane_id() == 0) set_error(err, kErrArg);
   return bj >= 0 ? key_index(bj) : -1;
 }
 

@@ -3,6 +3,7 @@ estimates over every split of the queries into blocks, against the oracle, bit f
 
 from __future__ import annotations
 
+import dataclasses
 import os
 import sys
 
@@ -15,7 +16,8 @@ pytestmark = pytest.mark.gpu
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 from gpu_util import DEV, T, assert_state_equal, bits  # noqa: E402
 from oracle import oracle as O  # noqa: E402
-from paper_2607_18253_amd import context_for  # noqa: E402
+from paper_2607_18253_amd import LarError, context_for  # noqa: E402
+from paper_2607_18253_amd.lar import LAR_E_ARG, LAR_E_STATE  # noqa: E402
 from workloads import make_tiny_workload  # noqa: E402
 from workloads.gen import make_tiny_sched_workload  # noqa: E402
 
@@ -76,3 +78,33 @@ def test_estimate_chunks(n_inst, n_q):
     np.testing.assert_array_equal(bits(tt.cpu().numpy()[0]), bits(np.asarray(ref_t)[row]))
     np.testing.assert_array_equal(it.cpu().numpy()[0], np.asarray(ref_i)[row])
     ctx.close()
+
+
+@pytest.mark.parametrize("n_inst", [3, 3000])
+def test_step_reports_the_first_kind_of_error(n_inst):
+    """One step that finds errors of different kinds reports what separate calls would: an
+    instance behind t (the estimate's trajectory) before a prompt out of range (the
+    estimate) before an iteration cap (the commit's replay)."""
+    wl = make_tiny_workload(900, n_inst=n_inst, n_q=2, max_res=5)
+    f64, i32 = torch.float64, torch.int32
+    acc, cost = T(wl.acc[0], f64), T(wl.cost[0], f64)
+    wc, w_lat = T(wl.w_cost, f64), T(wl.w_lat_ms, f64)
+
+    def step(ctx, p, t, t_next):
+        ctx.route_step(T([p], i32), T([4], i32), T([t], f64), T([t_next], f64), acc, cost, wc, w_lat)
+        with pytest.raises(LarError) as ei:
+            ctx.sync()
+        return ei.value.code
+
+    bad = wl.max_prompt + 1
+    clocks = np.zeros(n_inst)
+    clocks[n_inst - 1] = -5.0   # the last instance alone is behind
+    behind = dataclasses.replace(wl, clock_ms=clocks)
+    print(f"step errors: {n_inst} instances", flush=True)
+    for _ in range(5):
+        ctx = context_for(behind)
+        assert step(ctx, bad, 0.0, 1.0) == LAR_E_STATE
+        ctx.close()
+        ctx = context_for(wl, max_iters=3)
+        assert step(ctx, bad, 0.0, 1e9) == LAR_E_ARG
+        ctx.close()
