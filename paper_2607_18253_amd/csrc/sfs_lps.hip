@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256) void k_lps_wait(const lar_lps_params* prm, int
 // the thread keeps its instance's W, theta and t_dec (24 bytes out of its 64-byte
 // parameter record) in registers for the chunk's queries, and the block writes 256
 // consecutive estimates per query.  Read per estimate, the records were eight times the
-// bytes written: 4096 x 1024, 15.0 -> 9.1 us (3.7 TB/s of writes).
+// bytes written: 4096 x 1024, 15.0 -> 9.1-9.6 us (3.5-3.7 TB/s of writes).
 constexpr int kLpsChunk = 16;
 
 __global__ __launch_bounds__(256) void k_lps_est(const lar_lps_params* prm, const double* wait,
